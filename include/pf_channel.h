@@ -364,7 +364,8 @@ pf_status pf_run_batched(int32_t count, const pf_task *tasks, int32_t lanes, voi
  * correction's right-hand side of PF_FP32_REFINE (the float64 residual
  * formed in x-spectral space); PF_STAGE_PROJECT is the velocity and pressure
  * update of poisson_project (whose first x pass, which forms the divergence,
- * counts as PF_STAGE_XFWD). */
+ * counts as PF_STAGE_XFWD). PF_STAGE_ZERO_MODE has no launches of its own:
+ * the singular mode is part of the y forward and the z solve. */
 enum {
   PF_STAGE_XFWD = 0, PF_STAGE_YFWD = 1, PF_STAGE_ZSOLVE = 2, PF_STAGE_YINV = 3,
   PF_STAGE_XINV = 4, PF_STAGE_ZERO_MODE = 5, PF_STAGE_XFWD_RESID = 6, PF_STAGE_XINV_FINAL = 7,

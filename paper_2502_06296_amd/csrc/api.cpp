@@ -242,7 +242,7 @@ struct pf_poisson_plan {
   int xshape = 0, yshape = 0;  // launch shapes of the periodic x and y transforms
   DevArena ar;
   size_t o_zal, o_zga, o_zex, o_dzf, o_sx, o_sxb, o_sy, o_twx_d, o_twy_d, o_sums, o_sump,
-      o_fbar, o_m, o_zm, o_p0m, o_rdzf, o_rdzc, o_ctw, o_ctwx;
+      o_fbar, o_m, o_zm, o_rdzf, o_rdzc, o_ctw, o_ctwx;
   int ybc = PF_Y_PERIODIC, xbc = PF_X_PERIODIC;
   void *ws = nullptr;
   size_t ws_bytes = 0, ws_need = 0;
@@ -510,7 +510,6 @@ static pf_status channel_plan(pf_poisson_plan **out, const pf_grid *g, int32_t p
   pl->o_fbar = A.add<double>(nullptr, (size_t)nzu);
   pl->o_m = A.add<double>(nullptr, (size_t)nzu);
   pl->o_zm = A.add<double>(nullptr, (size_t)nzu);
-  pl->o_p0m = A.add<double>(nullptr, (size_t)nzu);
   pl->o_rdzf = A.add(rdzf.data(), rdzf.size());
   pl->o_rdzc = A.add(rdzc.data(), rdzc.size());
   A.cap = A.used;
@@ -639,6 +638,13 @@ static pf_status poisson_enqueue_plain(pf_poisson_plan *pl, const double *rhs, d
   double *fbar = A.at<double>(pl->o_fbar), *mm = A.at<double>(pl->o_m), *zm = A.at<double>(pl->o_zm);
   Timing &tm = pl->tm;
   pf_status s;
+  // the zero mode: its plane means in the y forward, its solve in the z solve
+  pf::PlaneMean pm;
+  pf::ZeroJob zj;
+  if (!helm) {
+    pm = pf::PlaneMean{sums, nullptr, fbar, 1.0 / ((double)nx * ny)};
+    zj = pf::ZeroJob{fbar, dzf, mm};
+  }
   if (pl->prec == PF_FP64) {
     const double2 *twx = A.at<double2>(pl->o_twx_d), *twy = A.at<double2>(pl->o_twy_d);
     const double2 *ctw = pl->ybc != PF_Y_PERIODIC ? A.at<double2>(pl->o_ctw) : nullptr;
@@ -650,9 +656,8 @@ static pf_status poisson_enqueue_plain(pf_poisson_plan *pl, const double *rhs, d
     const size_t sd = (size_t)nx * ny;
     STAGE(PF_STAGE_XFWD, div ? pf::launch_xfwd_div<double>(nx, ny, nz, *div, p, sd, twx, sums, st)
                              : pf::launch_xfwd<double>(nx, ny, rhs, p, sd, twx, sums, lines, st, xw, ctwx, xs));
-    if (!helm) STAGE(PF_STAGE_ZERO_MODE, pf::launch_zero_mode(nx, ny, nz, sums, dzf, zal, zga, fbar, mm, st));
-    STAGE(PF_STAGE_YFWD, pf::launch_yfwd<double>(nx, ny, nz, p, sd, twy, ctw, yw, st, xr, ys));
-    STAGE(PF_STAGE_ZSOLVE, pf::launch_zsolve<double>(nx, ny, nz, p, sd, zal, zga, zex, sx, sy, pl->zchunk, st, xr));
+    STAGE(PF_STAGE_YFWD, pf::launch_yfwd<double>(nx, ny, nz, p, sd, twy, ctw, yw, st, xr, ys, pm));
+    STAGE(PF_STAGE_ZSOLVE, pf::launch_zsolve<double>(nx, ny, nz, p, sd, zal, zga, zex, sx, sy, pl->zchunk, st, xr, zj));
     STAGE(PF_STAGE_YINV, pf::launch_yinv<double>(nx, ny, nz, p, sd, twy, ctw, yw, st, xr, ys));
     STAGE(PF_STAGE_XINV, (pf::launch_xinv<double, double>(nx, ny, p, sd, p, twx, helm ? zm : mm, nullptr, oscale,
                                                           lines, st, nullptr, xw, ctwx, xs)));
@@ -669,9 +674,8 @@ static pf_status poisson_enqueue_plain(pf_poisson_plan *pl, const double *rhs, d
   if (pl->prec == PF_FP32) {
     STAGE(PF_STAGE_XFWD, div ? pf::launch_xfwd_div<float>(nx, ny, nz, *div, W0, sp, twx, sums, st)
                              : pf::launch_xfwd<float>(nx, ny, rhs, W0, sp, twx, sums, lines, st, xw, ctwx, xs));
-    if (!helm) STAGE(PF_STAGE_ZERO_MODE, pf::launch_zero_mode(nx, ny, nz, sums, dzf, zal, zga, fbar, mm, st));
-    STAGE(PF_STAGE_YFWD, pf::launch_yfwd<float>(nx, ny, nz, W0, sp, twy, ctw, yw, st, xr, ys));
-    STAGE(PF_STAGE_ZSOLVE, pf::launch_zsolve<float>(nx, ny, nz, W0, sp, zal, zga, zex, sx, sy, pl->zchunk, st, xr));
+    STAGE(PF_STAGE_YFWD, pf::launch_yfwd<float>(nx, ny, nz, W0, sp, twy, ctw, yw, st, xr, ys, pm));
+    STAGE(PF_STAGE_ZSOLVE, pf::launch_zsolve<float>(nx, ny, nz, W0, sp, zal, zga, zex, sx, sy, pl->zchunk, st, xr, zj));
     STAGE(PF_STAGE_YINV, pf::launch_yinv<float>(nx, ny, nz, W0, sp, twy, ctw, yw, st, xr, ys));
     STAGE(PF_STAGE_XINV_FINAL, (pf::launch_xinv<float, double>(nx, ny, W0, sp, p, twx, helm ? zm : mm, nullptr,
                                                                oscale, lines, st, nullptr, xw, ctwx, xs)));
@@ -714,16 +718,24 @@ static pf_status poisson_enqueue_refined(pf_poisson_plan *pl, const double *rhs,
   } else {
     STAGE(PF_STAGE_XFWD, pf::launch_xfwd<float>(nx, ny, rhs, W0, sp, twx, sums, lines, st, xw, ctwx, xs));
   }
-  if (!helm) STAGE(PF_STAGE_ZERO_MODE, pf::launch_zero_mode(nx, ny, nz, sums, dzf, zal, zga, fbar, mm, st));
-  STAGE(PF_STAGE_YFWD, pf::launch_yfwd<float>(nx, ny, nz, W0, sp, twy, ctw, yw, st, xr, ys));
-  STAGE(PF_STAGE_ZSOLVE, pf::launch_zsolve<float>(nx, ny, nz, W0, sp, zal, zga, zex, sx, sy, pl->zchunk, st, xr));
+  // the zero mode: the plane means of f in the first y forward, its solve in
+  // the first z solve, the iterate's plane means in the second y forward
+  const double inv = 1.0 / ((double)nx * ny);
+  pf::PlaneMean pm, pm2;
+  pf::ZeroJob zj;
+  if (!helm) {
+    pm = pf::PlaneMean{sums, nullptr, fbar, inv};
+    zj = pf::ZeroJob{fbar, dzf, mm};
+    pm2 = pf::PlaneMean{sump, mm, zm, inv};
+  }
+  STAGE(PF_STAGE_YFWD, pf::launch_yfwd<float>(nx, ny, nz, W0, sp, twy, ctw, yw, st, xr, ys, pm));
+  STAGE(PF_STAGE_ZSOLVE, pf::launch_zsolve<float>(nx, ny, nz, W0, sp, zal, zga, zex, sx, sy, pl->zchunk, st, xr, zj));
   STAGE(PF_STAGE_YINV, pf::launch_yinv<float>(nx, ny, nz, W0, sp, twy, ctw, yw, st, xr, ys));
   const double idy2 = (double)ny * ny / (pl->ly * pl->ly);
   STAGE(PF_STAGE_XFWD_RESID,
         pf::launch_resid_spec(nx, ny, nz, rhs, fbar, W0, W1, sp, twx, sump, sx, zal, zga, zex, idy2,
                              pl->ybc, st, xw, ctwx, xs));
-  if (!helm) STAGE(PF_STAGE_ZERO_MODE, pf::launch_zero_shift(nx, ny, nz, sump, mm, A.at<double>(pl->o_p0m), zm, st));
-  STAGE(PF_STAGE_YFWD, pf::launch_yfwd<float>(nx, ny, nz, W1, sp, twy, ctw, yw, st, xr, ys));
+  STAGE(PF_STAGE_YFWD, pf::launch_yfwd<float>(nx, ny, nz, W1, sp, twy, ctw, yw, st, xr, ys, pm2));
   STAGE(PF_STAGE_ZSOLVE, pf::launch_zsolve<float>(nx, ny, nz, W1, sp, zal, zga, zex, sx, sy, pl->zchunk, st, xr));
   STAGE(PF_STAGE_YINV, pf::launch_yinv<float>(nx, ny, nz, W1, sp, twy, ctw, yw, st, xr, ys));
   STAGE(PF_STAGE_XINV_FINAL,
@@ -945,21 +957,6 @@ static pf_status poisson_enqueue_grouped(pf_poisson_plan *const *plans, const do
           J.sums = plans[t]->ar.at<double>(plans[t]->o_sums);
           return J;
         }, [&](GroupKey k, pf::GJobs &g) { return pf::launch_xfwd_grp(k.a, g, st); }));
-  // the zero modes of the Poisson plans (the 3-D Helmholtz has none)
-  std::vector<int> pois;
-  for (int t : ids)
-    if (!helm(t)) pois.push_back(t);
-  auto kone = [&](int) { return GroupKey{0, 0}; };
-  if (!pois.empty())
-    STAGE(PF_STAGE_ZERO_MODE, run_groups(pois, kone, [&](int t) {
-            pf::GJob J = base(t);
-            const pf_poisson_plan *pl = plans[t];
-            J.sums = pl->ar.at<double>(pl->o_sums);
-            J.out = pl->ar.at<double>(pl->o_fbar);
-            J.in2 = pl->ar.at<double>(pl->o_m);
-            J.aux = pl->ar.at<double>(pl->o_dzf);
-            return J;
-          }, [&](GroupKey, pf::GJobs &g) { return pf::launch_zero_mode_grp(g, st); }));
   // y forward, z solve, y inverse of one work array
   auto yzy = [&](bool second) -> pf_status {
     auto wj = [&](int t) {
@@ -968,15 +965,33 @@ static pf_status poisson_enqueue_grouped(pf_poisson_plan *const *plans, const do
       J.out = second ? W1(t) : W0(t);
       return J;
     };
+    // the y forward takes the plane means along, of f or of the iterate (the
+    // 3-D Helmholtz has no zero mode)
+    auto yj = [&](int t) {
+      pf::GJob J = wj(t);
+      const pf_poisson_plan *pl = plans[t];
+      if (helm(t)) return J;
+      J.sums = pl->ar.at<double>(second ? pl->o_sump : pl->o_sums);
+      J.in2 = second ? pl->ar.at<double>(pl->o_m) : nullptr;
+      J.zm = pl->ar.at<double>(second ? pl->o_zm : pl->o_fbar);
+      J.scale = 1.0 / ((double)pl->nx * pl->ny);
+      return J;
+    };
+    // the first z solve takes the zero mode's solve along
     auto zj = [&](int t) {
       pf::GJob J = base(t);
+      const pf_poisson_plan *pl = plans[t];
       J.out = second ? W1(t) : W0(t);
-      J.P = pf::zsolve_chunks(plans[t]->zchunk, plans[t]->nz);
+      J.P = pf::zsolve_chunks(pl->zchunk, pl->nz);
+      if (second || helm(t)) return J;
+      J.zm = pl->ar.at<double>(pl->o_fbar);
+      J.aux = pl->ar.at<double>(pl->o_dzf);
+      J.in2 = pl->ar.at<double>(pl->o_m);
       return J;
     };
     pf_status s2;
     if ((s2 = run_stage(tm, st, PF_STAGE_YFWD, [&]() {
-           return run_groups(ids, ky, wj, [&](GroupKey k, pf::GJobs &g) { return pf::launch_yfwd_grp(k.a, g, st); });
+           return run_groups(ids, ky, yj, [&](GroupKey k, pf::GJobs &g) { return pf::launch_yfwd_grp(k.a, g, st); });
          })))
       return s2;
     if ((s2 = run_stage(tm, st, PF_STAGE_ZSOLVE, [&]() {
@@ -1000,16 +1015,6 @@ static pf_status poisson_enqueue_grouped(pf_poisson_plan *const *plans, const do
           J.idy2 = (double)pl->ny * pl->ny / (pl->ly * pl->ly);
           return J;
         }, [&](GroupKey k, pf::GJobs &g) { return pf::launch_resid_grp(k.a, g, st); }));
-  if (!pois.empty())
-    STAGE(PF_STAGE_ZERO_MODE, run_groups(pois, kone, [&](int t) {
-            pf::GJob J = base(t);
-            const pf_poisson_plan *pl = plans[t];
-            J.sums = pl->ar.at<double>(pl->o_sump);
-            J.out = pl->ar.at<double>(pl->o_p0m);
-            J.in2 = pl->ar.at<double>(pl->o_m);
-            J.zm = pl->ar.at<double>(pl->o_zm);
-            return J;
-          }, [&](GroupKey, pf::GJobs &g) { return pf::launch_zero_shift_grp(g, st); }));
   if ((s = yzy(true))) return s;
   // one x inverse of W0 + W1 with the zero-mode profile
   STAGE(PF_STAGE_XINV_FINAL, run_groups(ids, kx, [&](int t) {

@@ -427,12 +427,26 @@ __device__ __forceinline__ void yinv_join_load(cplx<double> *lds, const T *base,
   }
 }
 
+// The mean of plane k from its `rows` line sums, by the first wave of a
+// workgroup: a fixed order of additions, no LDS and no barrier.
+__device__ __forceinline__ void plane_mean(const PlaneMean &pm, int k, int rows) {
+  if (!pm.sums || threadIdx.x >= 64) return;
+  const double *s = pm.sums + (size_t)k * rows;
+  double a = 0.0;
+#pragma unroll 4
+  for (int j = threadIdx.x; j < rows; j += 64) a += s[j];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+  if (threadIdx.x == 0) pm.out[k] = pm.m ? pm.m[k] - a * pm.inv : a * pm.inv;
+}
+
 template <typename T, int N, int TPL, int LPW, int YW, bool XR = false, int RO = 0>
 __device__ __forceinline__ void yfwd_body(T *__restrict__ data,
                                                    const cplx<double> *__restrict__ tw,
                                                    const cplx<double> *__restrict__ ctw, int nx,
-                                                   int nib, size_t sp,
+                                                   int nib, size_t sp, const PlaneMean &pm,
                                           unsigned bx_, unsigned gx_) {
+  static_assert(TPL * LPW >= 64, "a whole wave takes the plane mean");
   using C = cplx<double>;
   static_assert(N % (2 * TPL) == 0, "every thread takes N / TPL positions");
   __shared__ C lds[LPW * y_stride(N)];
@@ -441,6 +455,7 @@ __device__ __forceinline__ void yfwd_body(T *__restrict__ data,
   const unsigned blk = xcd_block(bx_, gx_);
   const int ib = blk % nib;
   const long k = blk / nib;
+  if (ib == 0) plane_mean(pm, (int)k, N);
   T *base = data + (size_t)k * sp + (size_t)ib * 2 * LPW;
   // lines run fastest across the lanes, so the first pass's reads (and the
   // last pass's writes) of row y cover the 2*LPW contiguous slots
@@ -488,8 +503,8 @@ template <typename T, int N, int TPL, int LPW, int YW, bool XR = false, int RO =
 __global__ __launch_bounds__(TPL *LPW) void k_yfwd(T *__restrict__ data,
                                                    const cplx<double> *__restrict__ tw,
                                                    const cplx<double> *__restrict__ ctw, int nx,
-                                                   int nib, size_t sp) {
-  yfwd_body<T, N, TPL, LPW, YW, XR, RO>(data, tw, ctw, nx, nib, sp, blockIdx.x, gridDim.x);
+                                                   int nib, size_t sp, PlaneMean pm) {
+  yfwd_body<T, N, TPL, LPW, YW, XR, RO>(data, tw, ctw, nx, nib, sp, pm, blockIdx.x, gridDim.x);
 }
 
 // ------------------------------------------------------------- y inverse
@@ -589,7 +604,7 @@ __device__ __forceinline__ long pf_round_block(long i, long G, long nblk) {
 template <typename T, int N, int TPL, int LPW, bool INV>
 __global__ __launch_bounds__(TPL *LPW) void k_y_persist(T *__restrict__ data,
                                                         const cplx<double> *__restrict__ tw, int nx,
-                                                        int nib, size_t sp, long nblk) {
+                                                        int nib, size_t sp, long nblk, PlaneMean pm) {
   using C = cplx<double>;
   using F = FirstPass<N, TPL, 0>;
   static_assert(N % (2 * TPL) == 0, "every thread takes N / TPL positions");
@@ -612,6 +627,7 @@ __global__ __launch_bounds__(TPL *LPW) void k_y_persist(T *__restrict__ data,
   for (long i = 0;; ++i) {
     const int ib = (int)(blk % nib);
     T *base = at(blk);
+    if (!INV && ib == 0) plane_mean(pm, (int)(blk / nib), N);
     const long nb = pf_round_block(i + 1, G, nblk);
     const bool more = nb < nblk;  // uniform
     // the thread's positions as values the compiler cannot carry from one

@@ -287,8 +287,9 @@ template <int N, int TPL, int LPW>
 __global__ __launch_bounds__(TPL *LPW) void k_yfwd_grp(const GJobs g) {
   const GJob &J = g.j[blockIdx.y];
   if (blockIdx.x >= J.nblk) return;
+  const PlaneMean pm{J.sums, static_cast<const double *>(J.in2), const_cast<double *>(J.zm), J.scale};
   yfwd_body<float, N, TPL, LPW, 0, false>(static_cast<float *>(J.out), J.tw, nullptr, J.nx,
-                                          J.nx / (2 * LPW), J.sp, blockIdx.x, J.nblk);
+                                          J.nx / (2 * LPW), J.sp, pm, blockIdx.x, J.nblk);
 }
 template <int N, int TPL, int LPW>
 __global__ __launch_bounds__(TPL *LPW) void k_yinv_grp(const GJobs g) {
@@ -426,7 +427,8 @@ hipError_t launch_resid_spec(int nx, int ny, int nz, const double *f, const doub
 
 template <typename T>
 hipError_t launch_yfwd(int nx, int ny, int nz, T *data, size_t sp, const cplx<double> *tw,
-                       const cplx<double> *ctw, int yw, hipStream_t st, bool xr, int shape) {
+                       const cplx<double> *ctw, int yw, hipStream_t st, bool xr, int shape,
+                       const PlaneMean &pm) {
   if (yw == 3) {
     // a field on the y faces: one FFT of twice the rows per column
     if (shape != 0) return hipErrorInvalidValue;
@@ -437,7 +439,7 @@ hipError_t launch_yfwd(int nx, int ny, int nz, T *data, size_t sp, const cplx<do
     if (nx % (2 * LPW)) return hipErrorInvalidValue;                                          \
     const int nib = nx / (2 * LPW);                                                           \
     hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 3>), dim3((unsigned)((long)nib * nz)),          \
-                       dim3(TPL * LPW), 0, st, data, tw, ctw, nx, nib, sp);                   \
+                       dim3(TPL * LPW), 0, st, data, tw, ctw, nx, nib, sp, PlaneMean{});      \
     return hipGetLastError();                                                                 \
   }
       PF_FOR_FFT_SIZES_Y(PF_CASE)
@@ -448,8 +450,8 @@ hipError_t launch_yfwd(int nx, int ny, int nz, T *data, size_t sp, const cplx<do
   }
   if (shape != 0) {
     if (yw != 0 || xr) return hipErrorInvalidValue;
-    if (shape == kYPersistShape) return launch_y_persist<T>(false, nx, ny, nz, data, sp, tw, st);
-    return launch_y_alt<T>(false, shape, nx, ny, nz, data, sp, tw, st);
+    if (shape == kYPersistShape) return launch_y_persist<T>(false, nx, ny, nz, data, sp, tw, st, pm);
+    return launch_y_alt<T>(false, shape, nx, ny, nz, data, sp, tw, st, pm);
   }
   switch (ny) {
 #define PF_CASE(N)                                                                            \
@@ -461,16 +463,16 @@ hipError_t launch_yfwd(int nx, int ny, int nz, T *data, size_t sp, const cplx<do
     if (yw != 0 && !ctw) return hipErrorInvalidValue;                                         \
     if (yw == 1)                                                                              \
       hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 1>), g, b, 0, st, data, tw, ctw, nx, nib,    \
-                         sp);                                                                 \
+                         sp, pm);                                                             \
     else if (yw == 2)                                                                         \
       hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 2>), g, b, 0, st, data, tw, ctw, nx, nib,    \
-                         sp);                                                                 \
+                         sp, pm);                                                             \
     else if (xr)                                                                              \
       hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 0, true>), g, b, 0, st, data, tw, ctw, nx,   \
-                         nib, sp);                                                            \
+                         nib, sp, pm);                                                        \
     else                                                                                      \
       hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 0>), g, b, 0, st, data, tw, ctw, nx, nib,    \
-                         sp);                                                                 \
+                         sp, pm);                                                               \
     return hipGetLastError();                                                                 \
   }
     PF_FOR_FFT_SIZES_Y(PF_CASE)
@@ -702,9 +704,9 @@ template hipError_t launch_xfwd<float>(int, int, const double *, float *, size_t
                                        const cplx<double> *, double *, long, hipStream_t, int,
                                        const cplx<double> *, int);
 template hipError_t launch_yfwd<double>(int, int, int, double *, size_t, const cplx<double> *,
-                                        const cplx<double> *, int, hipStream_t, bool, int);
+                                        const cplx<double> *, int, hipStream_t, bool, int, const PlaneMean &);
 template hipError_t launch_yfwd<float>(int, int, int, float *, size_t, const cplx<double> *,
-                                       const cplx<double> *, int, hipStream_t, bool, int);
+                                        const cplx<double> *, int, hipStream_t, bool, int, const PlaneMean &);
 template hipError_t launch_yinv<double>(int, int, int, double *, size_t, const cplx<double> *,
                                         const cplx<double> *, int, hipStream_t, bool, int);
 template hipError_t launch_yinv<float>(int, int, int, float *, size_t, const cplx<double> *,

@@ -42,7 +42,8 @@ hipError_t resid_one(int ny, int nz, const double *f, const double *fbar, const 
 }
 
 template <typename T, int N, int S>
-hipError_t y_one(bool inv, int nx, int nz, T *data, size_t sp, const cplx<double> *tw, hipStream_t st) {
+hipError_t y_one(bool inv, int nx, int nz, T *data, size_t sp, const cplx<double> *tw, hipStream_t st,
+                 const PlaneMean &pm) {
   constexpr TShape h = y_shape<T>(N, S);
   if constexpr (h.ok) {
     if (nx % (2 * h.lpw)) return hipErrorInvalidValue;
@@ -53,7 +54,7 @@ hipError_t y_one(bool inv, int nx, int nz, T *data, size_t sp, const cplx<double
                          sp);
     else
       hipLaunchKernelGGL((k_yfwd<T, N, h.tpl, h.lpw, 0, false, h.ro>), g, b, 0, st, data, tw, nullptr, nx, nib,
-                         sp);
+                         sp, pm);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
@@ -118,12 +119,12 @@ hipError_t launch_resid_alt(int shape, int nx, int ny, int nz, const double *f, 
 
 template <typename T>
 hipError_t launch_y_alt(bool inv, int shape, int nx, int ny, int nz, T *data, size_t sp,
-                        const cplx<double> *tw, hipStream_t st) {
+                        const cplx<double> *tw, hipStream_t st, const PlaneMean &pm) {
 #define PF_DISPATCH_N(N)                                                                        \
   case N:                                                                                       \
-    if (shape == 1) return y_one<T, N, 1>(inv, nx, nz, data, sp, tw, st);                      \
-    if (shape == 2) return y_one<T, N, 2>(inv, nx, nz, data, sp, tw, st);                      \
-    if (shape == 3) return y_one<T, N, 3>(inv, nx, nz, data, sp, tw, st);                      \
+    if (shape == 1) return y_one<T, N, 1>(inv, nx, nz, data, sp, tw, st, pm);                  \
+    if (shape == 2) return y_one<T, N, 2>(inv, nx, nz, data, sp, tw, st, pm);                  \
+    if (shape == 3) return y_one<T, N, 3>(inv, nx, nz, data, sp, tw, st, pm);                  \
     return hipErrorInvalidValue;
   PF_DISPATCH(ny, )
 #undef PF_DISPATCH_N
@@ -151,9 +152,9 @@ template hipError_t launch_xfwd_alt<double>(int, int, int, const double *, doubl
 template hipError_t launch_xfwd_alt<float>(int, int, int, const double *, float *, size_t,
                                            const cplx<double> *, double *, long, hipStream_t);
 template hipError_t launch_y_alt<double>(bool, int, int, int, int, double *, size_t,
-                                         const cplx<double> *, hipStream_t);
+                                         const cplx<double> *, hipStream_t, const PlaneMean &);
 template hipError_t launch_y_alt<float>(bool, int, int, int, int, float *, size_t,
-                                        const cplx<double> *, hipStream_t);
+                                        const cplx<double> *, hipStream_t, const PlaneMean &);
 template hipError_t launch_xinv_alt<double, double>(int, int, int, const double *, size_t, double *,
                                                     const cplx<double> *, const double *,
                                                     const double *, double, long, hipStream_t,

@@ -22,7 +22,8 @@ int device_cus() {
 }
 
 template <typename T, int N, bool INV>
-hipError_t y_persist_one(int nx, int nz, T *data, size_t sp, const cplx<double> *tw, hipStream_t st) {
+hipError_t y_persist_one(int nx, int nz, T *data, size_t sp, const cplx<double> *tw, hipStream_t st,
+                         const PlaneMean &pm) {
   constexpr int TPL = y_tpl(N), LPW = y_lpw<T>(N);
   if (nx % (2 * LPW)) return hipErrorInvalidValue;
   const int nib = nx / (2 * LPW);
@@ -36,19 +37,19 @@ hipError_t y_persist_one(int nx, int nz, T *data, size_t sp, const cplx<double> 
   if (occ < 1 || cus < 1) return hipErrorInvalidValue;
   const long G = nblk < (long)cus * occ ? nblk : (long)cus * occ;
   hipLaunchKernelGGL((k_y_persist<T, N, TPL, LPW, INV>), dim3((unsigned)G), dim3(TPL * LPW), 0, st, data, tw, nx,
-                     nib, sp, nblk);
+                     nib, sp, nblk, pm);
   return hipGetLastError();
 }
 }  // namespace
 
 template <typename T>
 hipError_t launch_y_persist(bool inv, int nx, int ny, int nz, T *data, size_t sp, const cplx<double> *tw,
-                            hipStream_t st) {
+                            hipStream_t st, const PlaneMean &pm) {
   switch (ny) {
 #define PF_CASE(N)                                                                               \
   case N:                                                                                        \
-    return inv ? y_persist_one<T, N, true>(nx, nz, data, sp, tw, st)                             \
-               : y_persist_one<T, N, false>(nx, nz, data, sp, tw, st);
+    return inv ? y_persist_one<T, N, true>(nx, nz, data, sp, tw, st, pm)                         \
+               : y_persist_one<T, N, false>(nx, nz, data, sp, tw, st, pm);
     PF_FOR_FFT_SIZES_Y(PF_CASE)
 #undef PF_CASE
     default:
@@ -57,8 +58,8 @@ hipError_t launch_y_persist(bool inv, int nx, int ny, int nz, T *data, size_t sp
 }
 
 template hipError_t launch_y_persist<double>(bool, int, int, int, double *, size_t, const cplx<double> *,
-                                             hipStream_t);
+                                             hipStream_t, const PlaneMean &);
 template hipError_t launch_y_persist<float>(bool, int, int, int, float *, size_t, const cplx<double> *,
-                                            hipStream_t);
+                                            hipStream_t, const PlaneMean &);
 
 }  // namespace pf

@@ -21,6 +21,74 @@
 
 namespace pf {
 
+// ----------------------------------------------------------- zero mode
+// The (0,0) slot of the transformed problem is the plane-mean profile of p:
+// the plane means fbar projected onto the range of L_z (zero dzf-weighted
+// mean c removed), the singular Neumann system, zero dzf-weighted mean. Its
+// rows have no excess, so each of them is a flux balance,
+//   gamma_k dzf_k (m[k+1] - m[k]) = sum_{i<=k} dzf_i (fbar_i - c),
+// and the solve is two running sums: the fluxes, then m from its
+// differences. One wave does both, 16 rows a lane at most (nz <= 1024),
+// with shuffles and no LDS, in a workgroup of its own in front of the z
+// solve's. What bounds it is latency: as a launch of one thread's serial
+// sweeps it took 16 us at 64 planes and 60 us at 512 (and the plane means
+// another launch of 3-5 us); inside the z solve its few microseconds run
+// beside the columns.
+__device__ __forceinline__ double lane_sum(double v, int lanes) {
+  for (int o = lanes / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+// the sum of v over the lanes below this one
+__device__ __forceinline__ double lane_before(double v, int lanes) {
+  const int lane = threadIdx.x;
+  double s = v;
+  for (int o = 1; o < lanes; o <<= 1) {
+    const double t = __shfl_up(s, o);
+    if (lane >= o) s += t;
+  }
+  const double b = __shfl_up(s, 1);
+  return lane ? b : 0.0;
+}
+// Rows of a lane at most: nz <= 1024 over 64 lanes, and the z solve's smaller
+// workgroups (P chunks of M <= 16 rows, P TP threads with TP >= 4) leave half
+// of their threads or more: at most 2 M / TP rows each.
+constexpr int kZeroRows = 16;
+__device__ __forceinline__ void zero_solve(const ZeroJob &z, const double *zga, int nz) {
+  // the first 64 threads, or as many as a power of two of a smaller workgroup
+  int lanes = 64;
+  while (lanes > (int)blockDim.x) lanes >>= 1;
+  if ((int)threadIdx.x >= lanes) return;
+  const int rows = (nz + lanes - 1) / lanes, r0 = (int)threadIdx.x * rows;
+  double w = 0.0, wf = 0.0;
+  for (int q = 0; q < rows; ++q)
+    if (r0 + q < nz) {
+      w += z.dzf[r0 + q];
+      wf += z.dzf[r0 + q] * z.fbar[r0 + q];
+    }
+  const double wt = lane_sum(w, lanes), c = lane_sum(wf, lanes) / wt;
+  double fl = 0.0;
+  for (int q = 0; q < rows; ++q)
+    if (r0 + q < nz) fl += z.dzf[r0 + q] * (z.fbar[r0 + q] - c);
+  double g = lane_before(fl, lanes), x = 0.0, wm = 0.0;
+  double xs[kZeroRows];
+#pragma unroll
+  for (int q = 0; q < kZeroRows; ++q) {
+    xs[q] = x;
+    const int r = r0 + q;
+    if (q < rows && r < nz) {
+      const double d = z.dzf[r];
+      wm += d * x;
+      g += d * (z.fbar[r] - c);
+      if (r + 1 < nz) x += g / (zga[r] * d);
+    }
+  }
+  const double x0 = lane_before(x, lanes);
+  const double shift = lane_sum(wm + w * x0, lanes) / wt;
+#pragma unroll
+  for (int q = 0; q < kZeroRows; ++q)
+    if (q < rows && r0 + q < nz) z.m[r0 + q] = x0 + xs[q] - shift;
+}
+
 // ------------------------------------------------------- Poisson z solve
 // Thread (col, ch): column i = ib*TI + col of plane j, rows [ch*M, ch*M+M)
 // of the column. Columns are padded to P*M rows with identity rows (alpha =
@@ -65,12 +133,18 @@ __global__ __launch_bounds__(512, WAVES) void k_zsolve(TS *__restrict__ data, in
                                                  const double *__restrict__ zga,
                                                  const double *__restrict__ zex,
                                                  const double *__restrict__ sx,
-                                                 const double *__restrict__ sy, size_t sp) {
+                                                 const double *__restrict__ sy, size_t sp, ZeroJob zj) {
+  unsigned bx_ = blockIdx.x, gx_ = gridDim.x;
+  if (zj.m) {  // the first workgroup takes the zero mode
+    if (bx_ == 0) return zero_solve(zj, zga, nz);
+    --bx_;
+    --gx_;
+  }
   extern __shared__ double red[];  // [4][2P][TI]: alpha, gamma, eps, d of the reduced rows
   const int nr = 2 * P;
   double *RA = red, *RG = red + nr * TI, *RE = red + 2 * nr * TI, *RD = red + 3 * nr * TI;
   const int nib = nx / TI;
-  const int blk = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int blk = (int)xcd_block(bx_, gx_);
   const int ib = blk % nib;
   const int j = blk / nib;
   const int col = threadIdx.x % TI;
@@ -209,7 +283,13 @@ template <typename TS, int M, int TP, int NR, int WAVES, bool SK>
 __global__ __launch_bounds__(512, WAVES) void k_zsolve2(TS *data, int nx, int ny, int nz, int P,
                                                const double *zal, const double *zga,
                                                const double *zex, const double *sx,
-                                               const double *sy, size_t sp, int xr) {
+                                               const double *sy, size_t sp, int xr, ZeroJob zj) {
+  unsigned bx_ = blockIdx.x, gx_ = gridDim.x;
+  if (zj.m) {  // the first workgroup takes the zero mode
+    if (bx_ == 0) return zero_solve(zj, zga, nz);
+    --bx_;
+    --gx_;
+  }
   using V = cplx<TS>;  // the pair (column i, column i+1) of one row
   // LDS: the z tables of the column, (alpha, gamma) and eps of row
   // ch*M + q at [q*P + ch] (the chunks of one wave read consecutive
@@ -225,7 +305,7 @@ __global__ __launch_bounds__(512, WAVES) void k_zsolve2(TS *data, int nx, int ny
     tex[o] = zex[e];
   }
   const int nib = nx / (2 * TP);
-  const int blk = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int blk = (int)xcd_block(bx_, gx_);
   const int ib = blk % nib;
   const int j = blk / nib;
   const int pc = threadIdx.x % TP;
@@ -662,9 +742,15 @@ template <typename TS, int M, int TP, int NR, int WAVES, int MAXT = 512, bool TI
 __global__ __launch_bounds__(MAXT, WAVES) void k_zsolve3(TS *data, int nx, int ny, int nz, int P,
                                                       const double *zal, const double *zga,
                                                       const double *zex, const double *sx,
-                                                      const double *sy, size_t sp, int xr) {
+                                                      const double *sy, size_t sp, int xr, ZeroJob zj) {
+  unsigned bx = blockIdx.x, gx = gridDim.x;
+  if (zj.m) {  // the first workgroup takes the zero mode
+    if (bx == 0) return zero_solve(zj, zga, nz);
+    --bx;
+    --gx;
+  }
   zsolve3_body<TS, M, TP, NR, WAVES, MAXT, TILE, R, DB>(data, nx, ny, nz, P, zal, zga, zex, sx, sy, sp, xr,
-                                                        blockIdx.x, gridDim.x);
+                                                        bx, gx);
 }
 
 // one z-solve shape for several problems with the same chunk count (see
@@ -672,10 +758,17 @@ __global__ __launch_bounds__(MAXT, WAVES) void k_zsolve3(TS *data, int nx, int n
 template <int M, int TP, int NR, int WAVES, int MAXT, bool TILE, int R, bool DB = false>
 __global__ __launch_bounds__(MAXT, WAVES) void k_zsolve3_grp(const GJobs g) {
   const GJob &J = g.j[blockIdx.y];
-  if (blockIdx.x >= J.nblk) return;  // uniform per block
+  unsigned bx = blockIdx.x;
+  if (J.in2) {  // the job's first workgroup takes its zero mode
+    if (bx == 0)
+      return zero_solve(ZeroJob{J.zm, J.aux, const_cast<double *>(static_cast<const double *>(J.in2))}, J.zga,
+                        J.nz);
+    --bx;
+  }
+  if (bx >= J.nblk) return;  // uniform per block
   zsolve3_body<float, M, TP, NR, WAVES, MAXT, TILE, R, DB>(static_cast<float *>(J.out), J.nx, J.ny, J.nz,
                                                            J.P, J.zal, J.zga, J.zex, J.sx, J.sy, J.sp, 0,
-                                                           blockIdx.x, J.nblk);
+                                                           bx, J.nblk);
 }
 
 // Launch shapes of the z solve: rows per thread M, columns per workgroup
@@ -728,6 +821,13 @@ static const ZVariant kZVariants[] = {
     {16, 32, 0, true, true, 1, false, true, 512, false, 1, true},
 };
 constexpr int kZVariantCount = sizeof(kZVariants) / sizeof(kZVariants[0]);
+
+// the zero mode's rows fit the lanes of a workgroup of `threads`
+static bool zero_fits(int nz, int threads) {
+  int lanes = 64;
+  while (lanes > threads) lanes >>= 1;
+  return lanes > 0 && nz <= lanes * kZeroRows;
+}
 
 int zsolve_variant_count() { return kZVariantCount; }
 
@@ -796,17 +896,18 @@ int zsolve_default_variant(int nx, int nz, bool fp64) {
 template <typename TS>
 hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const double *zal,
                          const double *zga, const double *zex, const double *sx, const double *sy,
-                         int variant, hipStream_t st, bool xr) {
+                         int variant, hipStream_t st, bool xr, const ZeroJob &zj) {
   // the z tables hold whole 16-row chunks (identity padding past nz)
   if (!zsolve_variant_fits(variant, nx, nz, (int)sizeof(TS))) return hipErrorInvalidValue;
   const ZVariant &z = kZVariants[variant];
   const int P = (nz + z.M - 1) / z.M;
   const size_t shm = zsolve_lds(z, P, (int)sizeof(TS));
-  dim3 g((unsigned)((long)(nx / z.TI) * ny)), b(z.paired ? P * z.TI / 2 / z.rounds : P * z.TI);
+  dim3 g((unsigned)((long)(nx / z.TI) * ny) + (zj.m ? 1 : 0)), b(z.paired ? P * z.TI / 2 / z.rounds : P * z.TI);
+  if (zj.m && !zero_fits(nz, (int)b.x)) return hipErrorInvalidValue;
 #define PF_ZV(ID, M_, TI_, W_, F_)                                                                \
   case ID:                                                                                        \
     hipLaunchKernelGGL((k_zsolve<TS, M_, TI_, W_, F_>), g, b, shm, st, data, nx, ny, nz, P, zal, \
-                       zga, zex, sx, sy, sp);                                                         \
+                       zga, zex, sx, sy, sp, zj);                                                         \
     break;
   switch (variant) {
     PF_ZV(0, 16, 16, 0, false)
@@ -820,7 +921,7 @@ hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const doub
 #define PF_ZP(ID, M_, TI_, NR_, W_, SK_)                                                         \
   case ID:                                                                                       \
     hipLaunchKernelGGL((k_zsolve2<TS, M_, TI_ / 2, NR_, W_, SK_>), g, b, shm, st, data, nx, ny,  \
-                       nz, P, zal, zga, zex, sx, sy, sp, (int)xr);                                   \
+                       nz, P, zal, zga, zex, sx, sy, sp, (int)xr, zj);                                   \
     break;
     PF_ZP(8, 16, 16, 1, 1, true)
     PF_ZP(9, 8, 16, 1, 1, true)
@@ -835,7 +936,7 @@ hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const doub
 #define PF_ZS(ID, M_, TI_, W_)                                                                   \
   case ID:                                                                                       \
     hipLaunchKernelGGL((k_zsolve3<TS, M_, TI_ / 2, 1, W_>), g, b, shm, st, data, nx, ny, nz, P,  \
-                       zal, zga, zex, sx, sy, sp, (int)xr);                                          \
+                       zal, zga, zex, sx, sy, sp, (int)xr, zj);                                          \
     break;
     PF_ZS(18, 8, 8, 4)
     PF_ZS(19, 8, 16, 4)
@@ -849,14 +950,14 @@ hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const doub
 #define PF_ZW(ID, M_, TI_)                                                                       \
   case ID:                                                                                       \
     hipLaunchKernelGGL((k_zsolve3<TS, M_, TI_ / 2, 1, 1, 1024>), g, b, shm, st, data, nx, ny, nz, \
-                       P, zal, zga, zex, sx, sy, sp, (int)xr);                                   \
+                       P, zal, zga, zex, sx, sy, sp, (int)xr, zj);                                   \
     break;
     PF_ZW(27, 8, 32)
     PF_ZW(28, 8, 16)
 #define PF_ZT(ID, M_, TI_, MAXT_, R_)                                                            \
   case ID:                                                                                       \
     hipLaunchKernelGGL((k_zsolve3<TS, M_, TI_ / 2 / R_, 1, 1, MAXT_, true, R_>), g, b, shm, st,   \
-                       data, nx, ny, nz, P, zal, zga, zex, sx, sy, sp, (int)xr);                 \
+                       data, nx, ny, nz, P, zal, zga, zex, sx, sy, sp, (int)xr, zj);                 \
     break;
     PF_ZT(29, 8, 32, 1024, 2)
     PF_ZT(30, 16, 32, 512, 2)
@@ -868,19 +969,19 @@ hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const doub
     PF_ZT(36, 8, 32, 512, 2)
   case 37:
     hipLaunchKernelGGL((k_zsolve3<TS, 8, 8, 1, 1, 1024, true, 1, true>), g, b, shm, st, data, nx, ny, nz, P,
-                       zal, zga, zex, sx, sy, sp, (int)xr);
+                       zal, zga, zex, sx, sy, sp, (int)xr, zj);
     break;
   case 38:
     hipLaunchKernelGGL((k_zsolve3<TS, 8, 8, 1, 1, 1024, false, 1, true>), g, b, shm, st, data, nx, ny, nz, P,
-                       zal, zga, zex, sx, sy, sp, (int)xr);
+                       zal, zga, zex, sx, sy, sp, (int)xr, zj);
     break;
   case 39:
     hipLaunchKernelGGL((k_zsolve3<TS, 8, 8, 1, 1, 512, true, 1, true>), g, b, shm, st, data, nx, ny, nz, P,
-                       zal, zga, zex, sx, sy, sp, (int)xr);
+                       zal, zga, zex, sx, sy, sp, (int)xr, zj);
     break;
   case 40:
     hipLaunchKernelGGL((k_zsolve3<TS, 16, 16, 1, 1, 512, false, 1, true>), g, b, shm, st, data, nx, ny, nz,
-                       P, zal, zga, zex, sx, sy, sp, (int)xr);
+                       P, zal, zga, zex, sx, sy, sp, (int)xr, zj);
     break;
 #undef PF_ZT
 #undef PF_ZW
@@ -905,7 +1006,9 @@ hipError_t launch_zsolve_grp(int variant, GJobs &g, hipStream_t st) {
     if ((J.nz + z.M - 1) / z.M != P || J.P != P || !zsolve_variant_fits(variant, J.nx, J.nz, 4))
       return hipErrorInvalidValue;
     J.nblk = (unsigned)((long)(J.nx / z.TI) * J.ny);
-    mb = J.nblk > mb ? J.nblk : mb;
+    if (J.in2 && (!J.zm || !J.aux || !zero_fits(J.nz, P * z.TI / 2 / z.rounds))) return hipErrorInvalidValue;
+    const unsigned nb = J.nblk + (J.in2 ? 1 : 0);
+    mb = nb > mb ? nb : mb;
   }
   const size_t shm = zsolve_lds(z, P, 4);
   const dim3 gr(mb, (unsigned)g.count), b(P * z.TI / 2 / z.rounds);
@@ -954,159 +1057,10 @@ hipError_t launch_zsolve_grp(int variant, GJobs &g, hipStream_t st) {
 
 template hipError_t launch_zsolve<double>(int, int, int, double *, size_t, const double *, const double *,
                                           const double *, const double *, const double *, int,
-                                          hipStream_t, bool);
+                                          hipStream_t, bool, const ZeroJob &);
 template hipError_t launch_zsolve<float>(int, int, int, float *, size_t, const double *, const double *,
                                          const double *, const double *, const double *, int,
-                                         hipStream_t, bool);
-
-// ----------------------------------------------------------- zero mode
-// The (0,0) slot of the transformed problem is the plane-mean profile of p.
-// Plane means come from the float64 line sums, one workgroup per plane with
-// a fixed-order tree reduction (bitwise reproducible).
-__device__ __forceinline__ void plane_means_body(const double *__restrict__ sums, double *__restrict__ mean,
-                                                 int ny, double inv_nxny, int k) {
-  __shared__ double red[256];
-  const int tid = threadIdx.x;
-  const double *s = sums + (size_t)k * ny;
-  double a = 0.0;
-  for (int j = tid; j < ny; j += 256) a += s[j];
-  red[tid] = a;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
-  }
-  if (tid == 0) mean[k] = red[0] * inv_nxny;
-}
-__global__ __launch_bounds__(256) void k_plane_means(const double *__restrict__ sums,
-                                                     double *__restrict__ mean, int ny,
-                                                     double inv_nxny) {
-  plane_means_body(sums, mean, ny, inv_nxny, blockIdx.x);
-}
-
-// One thread: projection of the plane means fbar onto the range of L_z (zero
-// dzf-weighted mean), the singular Neumann system solved with its last
-// equation replaced by m[nz-1] = 0, then the shift to zero dzf-weighted mean.
-// With p0mean (the iterate's plane means) it writes zm = m - p0mean instead.
-__device__ __forceinline__ void zero_solve_body(const double *__restrict__ fbar, const double *__restrict__ dzf,
-                                                const double *__restrict__ zal, const double *__restrict__ zga,
-                                                double *__restrict__ m, int nz) {
-  extern __shared__ double sh[];  // F, W, A, G, Y, RT: nz each
-  double *F = sh, *W = sh + nz, *A = sh + 2 * nz, *G = sh + 3 * nz, *Y = sh + 4 * nz,
-         *RT = sh + 5 * nz;
-  for (int k = threadIdx.x; k < nz; k += blockDim.x) {
-    F[k] = fbar[k];
-    W[k] = dzf[k];
-    A[k] = zal[k];
-    G[k] = zga[k];
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  double wr = 0.0, w = 0.0;
-  for (int k = 0; k < nz; ++k) { wr += W[k] * F[k]; w += W[k]; }
-  const double c = wr / w;
-  // rows 0..nz-2 of -L_z x = -(fbar - c), x[nz-1] = 0 (row nz-2 keeps its
-  // gamma on the diagonal). No row has an excess, so the pivot of row k is
-  // gamma_k + g_k with g_0 = 0 and g_k = alpha_k g_{k-1} / pivot_{k-1}.
-  // pivots first (a chain of reciprocals only), then the right-hand side
-  double g = 0.0, rp = 0.0;
-  for (int k = 0; k < nz - 1; ++k) {
-    g = A[k] * g * rp;
-    rp = 1.0 / (G[k] + g);
-    RT[k] = rp;
-  }
-  double y = 0.0;
-  for (int k = 0; k < nz - 1; ++k) {
-    y = (-(F[k] - c) + A[k] * y) * RT[k];
-    Y[k] = y;
-    RT[k] = G[k] * RT[k];
-  }
-  double x = 0.0, wm = 0.0;
-  Y[nz - 1] = 0.0;
-  for (int k = nz - 2; k >= 0; --k) {
-    x = Y[k] + (k == nz - 2 ? 0.0 : RT[k] * x);
-    Y[k] = x;
-    wm += W[k] * x;
-  }
-  const double shift = wm / w;
-  for (int k = 0; k < nz; ++k) m[k] = Y[k] - shift;
-}
-__global__ __launch_bounds__(256) void k_zero_solve(const double *__restrict__ fbar,
-                                                    const double *__restrict__ dzf,
-                                                    const double *__restrict__ zal,
-                                                    const double *__restrict__ zga,
-                                                    double *__restrict__ m, int nz) {
-  zero_solve_body(fbar, dzf, zal, zga, m, nz);
-}
-
-__global__ __launch_bounds__(256) void k_sub(const double *__restrict__ a,
-                                             const double *__restrict__ b, double *__restrict__ out,
-                                             int n) {
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k < n) out[k] = a[k] - b[k];
-}
-
-// grouped: blockIdx.y (means) or blockIdx.x (solve, difference) is the job
-__global__ __launch_bounds__(256) void k_plane_means_grp(const GJobs g) {
-  const GJob &J = g.j[blockIdx.y];
-  if ((int)blockIdx.x >= J.nz) return;  // uniform per block
-  plane_means_body(J.sums, static_cast<double *>(J.out), J.ny, 1.0 / ((double)J.nx * J.ny), blockIdx.x);
-}
-__global__ __launch_bounds__(256) void k_zero_solve_grp(const GJobs g) {
-  const GJob &J = g.j[blockIdx.x];
-  zero_solve_body(static_cast<const double *>(J.out), J.aux, J.zal, J.zga,
-                  const_cast<double *>(static_cast<const double *>(J.in2)), J.nz);
-}
-__global__ __launch_bounds__(256) void k_sub_grp(const GJobs g) {
-  const GJob &J = g.j[blockIdx.y];
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k < J.nz)
-    const_cast<double *>(J.zm)[k] = static_cast<const double *>(J.in2)[k] - static_cast<const double *>(J.out)[k];
-}
-hipError_t launch_zero_mode_grp(GJobs &g, hipStream_t st) {
-  if (g.count < 1 || g.count > kMaxGroupJobs) return hipErrorInvalidValue;
-  int mz = 1;
-  for (int k = 0; k < g.count; ++k) mz = g.j[k].nz > mz ? g.j[k].nz : mz;
-  hipLaunchKernelGGL(k_plane_means_grp, dim3(mz, g.count), dim3(256), 0, st, g);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_zero_solve_grp, dim3(g.count), dim3(256), (size_t)6 * mz * sizeof(double), st, g);
-  return hipGetLastError();
-}
-hipError_t launch_zero_shift_grp(GJobs &g, hipStream_t st) {
-  if (g.count < 1 || g.count > kMaxGroupJobs) return hipErrorInvalidValue;
-  int mz = 1;
-  for (int k = 0; k < g.count; ++k) mz = g.j[k].nz > mz ? g.j[k].nz : mz;
-  hipLaunchKernelGGL(k_plane_means_grp, dim3(mz, g.count), dim3(256), 0, st, g);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sub_grp, dim3((mz + 255) / 256, g.count), dim3(256), 0, st, g);
-  return hipGetLastError();
-}
-
-hipError_t launch_zero_mode(int nx, int ny, int nz, const double *sums, const double *dzf,
-                            const double *zal, const double *zga, double *fbar, double *m,
-                            hipStream_t st) {
-  const double inv = 1.0 / ((double)nx * (double)ny);
-  hipLaunchKernelGGL(k_plane_means, dim3(nz), dim3(256), 0, st, sums, fbar, ny, inv);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_zero_solve, dim3(1), dim3(256), (size_t)6 * nz * sizeof(double), st, fbar,
-                     dzf, zal, zga, m, nz);
-  return hipGetLastError();
-}
-
-// zm = m - (plane means of the iterate p0), from its float64 line sums;
-// p0mean is scratch of nz doubles.
-hipError_t launch_zero_shift(int nx, int ny, int nz, const double *sums_p0, const double *m,
-                             double *p0mean, double *zm, hipStream_t st) {
-  const double inv = 1.0 / ((double)nx * (double)ny);
-  hipLaunchKernelGGL(k_plane_means, dim3(nz), dim3(256), 0, st, sums_p0, p0mean, ny, inv);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sub, dim3((nz + 255) / 256), dim3(256), 0, st, m, p0mean, zm, nz);
-  return hipGetLastError();
-}
+                                         hipStream_t, bool, const ZeroJob &);
 
 // ------------------------------------------------------- Helmholtz apply
 // Algorithm 2, Steps 2-4, with the Step 1 coefficients of pcr_prepare. One

@@ -139,6 +139,23 @@ constexpr TShape y_shape(int n, int s) {
 // All return hipSuccess or the launch error. Lengths are runtime checked by
 // the caller against fft_size_supported.
 
+// The singular (0,0) mode needs no launch of its own. Its plane means come
+// from the float64 line sums an x pass leaves: the workgroup of slots 0 and 1
+// of every plane of the next y forward sums them (sums: ny of each plane)
+// and writes out[k] = mean, or m[k] - mean where m is given (the profile of a
+// refined solve minus the iterate's plane means). Null sums: nothing to do.
+struct PlaneMean {
+  const double *sums = nullptr, *m = nullptr;
+  double *out = nullptr;
+  double inv = 0.0;  // 1 / (nx ny)
+};
+// The pinned solve for its profile m from the plane means fbar, in the one
+// extra workgroup of the next z solve. Null m: nothing to do.
+struct ZeroJob {
+  const double *fbar = nullptr, *dzf = nullptr;
+  double *m = nullptr;
+};
+
 // Every transform runs in float64; T, TS and TO are storage types. A
 // packed spectrum array holds its z planes sp >= nx*ny elements apart (the
 // float32 work arrays are padded so that the z columns do not all fall on
@@ -175,9 +192,11 @@ hipError_t launch_resid_spec(int nx, int ny, int nz, const double *f, const doub
 // same function forward and inverse (the inverse leaves the factor 2 ny).
 // xr (periodic y): the x slots are real coefficients of x walls' transforms,
 // so every slot pair is split into two packed real y spectra.
+// pm: the plane means that the y forward takes along (PlaneMean below).
 template <typename T>
 hipError_t launch_yfwd(int nx, int ny, int nz, T *data, size_t sp, const cplx<double> *tw,
-                       const cplx<double> *ctw, int yw, hipStream_t st, bool xr = false, int shape = 0);
+                       const cplx<double> *ctw, int yw, hipStream_t st, bool xr = false, int shape = 0,
+                       const PlaneMean &pm = PlaneMean{});
 template <typename T>
 hipError_t launch_yinv(int nx, int ny, int nz, T *data, size_t sp, const cplx<double> *tw,
                        const cplx<double> *ctw, int yw, hipStream_t st, bool xr = false, int shape = 0);
@@ -203,11 +222,11 @@ hipError_t launch_resid_alt(int shape, int nx, int ny, int nz, const double *f, 
                             const double *zex, double idy2, int ywalls, hipStream_t st);
 template <typename T>
 hipError_t launch_y_alt(bool inv, int shape, int nx, int ny, int nz, T *data, size_t sp,
-                        const cplx<double> *tw, hipStream_t st);
+                        const cplx<double> *tw, hipStream_t st, const PlaneMean &pm = PlaneMean{});
 // the persistent y transforms (shape kYPersistShape, periodic x and y)
 template <typename T>
 hipError_t launch_y_persist(bool inv, int nx, int ny, int nz, T *data, size_t sp, const cplx<double> *tw,
-                            hipStream_t st);
+                            hipStream_t st, const PlaneMean &pm = PlaneMean{});
 template <typename TS, typename TO>
 hipError_t launch_xinv_alt(int shape, int nx, int ny, const TS *in, size_t sp, TO *out,
                            const cplx<double> *tw, const double *zm, const TS *in2, double scale,
@@ -253,7 +272,7 @@ hipError_t launch_project(int nx, int ny, int nz, const double *phi, double *u, 
 template <typename TS>
 hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const double *zal,
                          const double *zga, const double *zex, const double *sx, const double *sy,
-                         int variant, hipStream_t st, bool xr = false);
+                         int variant, hipStream_t st, bool xr = false, const ZeroJob &zj = ZeroJob{});
 int zsolve_variant_count();
 bool zsolve_variant_fits(int variant, int nx, int nz, int esize);  // esize: bytes per stored value
 int zsolve_default_variant(int nx, int nz, bool fp64);
@@ -266,7 +285,10 @@ int zsolve_default_variant(int nx, int nz, bool fp64);
 // one float64-residual correction, periodic x and y. The fields a stage
 // reads and writes:
 //   x forward:  in = f (float64), out = W (float32), sums = line sums
-//   y forward / inverse, z solve: out = W in place
+//   y forward / inverse, z solve: out = W in place; a y forward with plane
+//               means (PlaneMean): sums, in2 = m, zm = the means' output
+//               (written), scale = 1 / (nx ny); a z solve with the zero mode
+//               (ZeroJob): zm = fbar, aux = dzf, in2 = m (written)
 //   residual:   in = f, in2 = W (iterate), out = correction's right-hand
 //               side (float32), zm = fbar, sums = the iterate's line sums
 //   x inverse:  in = W, in2 = correction, out = p (float64), zm = zero-mode
@@ -282,7 +304,7 @@ struct GJob {
   const double *zm;
   const double *zal, *zga, *zex, *sx, *sy;
   unsigned long long *stat;
-  const double *aux;  // zero mode: dzf
+  const double *aux;
   double scale, idy2;
   size_t sp;
   int nx, ny, nz, P;
@@ -297,28 +319,11 @@ hipError_t launch_yfwd_grp(int ny, GJobs &g, hipStream_t st);
 hipError_t launch_yinv_grp(int ny, GJobs &g, hipStream_t st);
 hipError_t launch_resid_grp(int nx, GJobs &g, hipStream_t st);
 hipError_t launch_xinv_grp(int nx, GJobs &g, hipStream_t st);
-// the zero mode of every job: plane means fbar (out) of its line sums
-// (sums), then the pinned solve for the profile m (in2 -> written) from
-// fbar, dzf (aux), zal, zga; zero shift: plane means p0m (out) of the
-// iterate's sums, then zm (zm, written) = m (in2) - p0m
-hipError_t launch_zero_mode_grp(GJobs &g, hipStream_t st);
-hipError_t launch_zero_shift_grp(GJobs &g, hipStream_t st);
 // every job of the group runs z-solve `variant` (a separator-form shape)
 // with the same chunk count
 hipError_t launch_zsolve_grp(int variant, GJobs &g, hipStream_t st);
 bool zsolve_variant_groups(int variant);
 int zsolve_chunks(int variant, int nz);  // P of a variant for nz rows
-// Singular (0,0) mode: plane means fbar[nz] of the right-hand side from its
-// line sums, projection, pinned Neumann solve for the plane-mean profile
-// m[nz] of p.
-hipError_t launch_zero_mode(int nx, int ny, int nz, const double *sums, const double *dzf,
-                            const double *zal, const double *zga, double *fbar, double *m,
-                            hipStream_t st);
-// zm = m - plane means of an iterate (from its float64 line sums; p0mean is
-// nz doubles of scratch).
-hipError_t launch_zero_shift(int nx, int ny, int nz, const double *sums_p0, const double *m,
-                             double *p0mean, double *zm, hipStream_t st);
-
 // Helmholtz apply (Algorithm 2, Steps 2-4).
 struct HelmCoef {
   // per row r (n): forward multiplier alpha_r/b_{r-1}, backward multiplier
