@@ -18,6 +18,8 @@
 #include "fft_kernels.hpp"
 #include "pf_internal.hpp"
 
+#include <algorithm>
+
 namespace pf {
 
 bool fft_size_supported(int n) {
@@ -152,6 +154,14 @@ __global__ __launch_bounds__(TPL *LPW) void k_xfwd_div(DivArgs d, T *__restrict_
 // access is a 512-byte row segment and the x and y neighbours of phi come
 // from lines the neighbouring lanes and rows read. The Neumann rows have
 // alpha_0 = 0 and gamma_{nz-1} = 0, so the zeros past the walls drop out.
+// Bound by HBM where the columns alone fill the chip (512 x 384 x 256: 4.9
+// TB/s). With fewer than kProjectBlocks workgroups of columns the planes are
+// cut into chunks of kProjectPlanes or more, blockIdx.z, each of which reads
+// one plane of phi more: the whole substep at 192 x 96 x 100 (72 workgroups
+// of columns) went from 122 to 97 us; at 512 x 384 (768) a cut made it
+// slower, 2.26 -> 2.31 ms.
+constexpr long kProjectBlocks = 1024;
+constexpr int kProjectPlanes = 8;
 template <bool LZ>
 __global__ __launch_bounds__(256) void k_project(const double *__restrict__ phi,
                                                  double *__restrict__ u, double *__restrict__ v,
@@ -160,7 +170,8 @@ __global__ __launch_bounds__(256) void k_project(const double *__restrict__ phi,
                                                  const double *__restrict__ zga,
                                                  const double *__restrict__ rdzc, int nx, int ny,
                                                  int nz, double gx, double gy, double gdt, double c,
-                                                 int ywalls, int xwalls) {
+                                                 int ywalls, int xwalls, int kc) {
+  const int k0 = (int)blockIdx.z * kc, k1 = k0 + kc < nz ? k0 + kc : nz;
   const int i = blockIdx.x * 64 + (int)(threadIdx.x % 64);
   const int j = blockIdx.y * 4 + (int)(threadIdx.x / 64);
   if (i >= nx || j >= ny) return;  // no barrier follows
@@ -172,9 +183,9 @@ __global__ __launch_bounds__(256) void k_project(const double *__restrict__ phi,
   const size_t o = (size_t)j * nx + i;
   const size_t ox = (size_t)j * nx + (i + 1 == nx ? 0 : i + 1);
   const size_t oy = (size_t)(j + 1 == ny ? 0 : j + 1) * nx + i;
-  double fm = 0.0, f0 = phi[o];
+  double fm = LZ && k0 > 0 ? phi[(size_t)(k0 - 1) * plane + o] : 0.0, f0 = phi[(size_t)k0 * plane + o];
 #pragma unroll 2
-  for (int k = 0; k < nz; ++k) {
+  for (int k = k0; k < k1; ++k) {
     const size_t b = (size_t)k * plane;
     const bool up = k + 1 < nz;
     const double fp = up ? phi[b + plane + o] : 0.0;
@@ -260,14 +271,17 @@ hipError_t launch_project(int nx, int ny, int nz, const double *phi, double *u, 
                           double *w, double *p, const double *zal, const double *zga,
                           const double *rdzc, double gx, double gy, double gdt, double c,
                           bool ywalls, bool xwalls, hipStream_t st) {
-  dim3 g((unsigned)((nx + 63) / 64), (unsigned)((ny + 3) / 4));
+  const long cols = (long)((nx + 63) / 64) * ((ny + 3) / 4);
+  const int want = cols < kProjectBlocks ? (int)(kProjectBlocks / cols) : 1;
+  const int kc = std::max((nz + want - 1) / want, kProjectPlanes);
+  dim3 g((unsigned)((nx + 63) / 64), (unsigned)((ny + 3) / 4), (unsigned)((nz + kc - 1) / kc));
   const int yw = ywalls ? 1 : 0, xw = xwalls ? 1 : 0;
   if (c != 0.0)
     hipLaunchKernelGGL((k_project<true>), g, dim3(256), 0, st, phi, u, v, w, p, zal, zga, rdzc, nx,
-                       ny, nz, gx, gy, gdt, c, yw, xw);
+                       ny, nz, gx, gy, gdt, c, yw, xw, kc);
   else
     hipLaunchKernelGGL((k_project<false>), g, dim3(256), 0, st, phi, u, v, w, p, zal, zga, rdzc,
-                       nx, ny, nz, gx, gy, gdt, c, yw, xw);
+                       nx, ny, nz, gx, gy, gdt, c, yw, xw, kc);
   return hipGetLastError();
 }
 
