@@ -2,12 +2,8 @@
 // packed real layout of App. A).
 //
 // x direction: a workgroup takes LPW consecutive pairs of real x lines, so
-// every global access is a run of contiguous values. y direction: a
-// workgroup takes one z plane and 2*LPW adjacent x slots and transforms the
-// LPW complex columns formed by pairing neighbouring slots; each row access
-// is 2*LPW contiguous values (128 bytes by default). The x<->y permutation of
-// the pencil method is therefore never materialised: the y kernel gathers
-// its columns straight from the x-packed array and writes them back in place.
+// every global access is a run of contiguous values. The y direction:
+// kernels_fft_y.hip.
 //
 // Storage (HBM) is float64 or float32 (TS); the transforms themselves always
 // run in float64 in LDS and registers. A float32 butterfly network leaves
@@ -298,21 +294,6 @@ __global__ __launch_bounds__(TPL *LPW) void k_xfwd_grp(const GJobs g) {
                                          blockIdx.x, J.nblk);
 }
 template <int N, int TPL, int LPW>
-__global__ __launch_bounds__(TPL *LPW) void k_yfwd_grp(const GJobs g) {
-  const GJob &J = g.j[blockIdx.y];
-  if (blockIdx.x >= J.nblk) return;
-  const PlaneMean pm{J.sums, static_cast<const double *>(J.in2), const_cast<double *>(J.zm), J.scale};
-  yfwd_body<float, N, TPL, LPW, 0, false>(static_cast<float *>(J.out), J.tw, nullptr, J.nx,
-                                          J.nx / (2 * LPW), J.sp, pm, blockIdx.x, J.nblk);
-}
-template <int N, int TPL, int LPW>
-__global__ __launch_bounds__(TPL *LPW) void k_yinv_grp(const GJobs g) {
-  const GJob &J = g.j[blockIdx.y];
-  if (blockIdx.x >= J.nblk) return;
-  yinv_body<float, N, TPL, LPW, 0, false>(static_cast<float *>(J.out), J.tw, nullptr, J.nx,
-                                          J.nx / (2 * LPW), J.sp, blockIdx.x, J.nblk);
-}
-template <int N, int TPL, int LPW>
 __global__ __launch_bounds__(TPL *LPW) void k_resid_grp(const GJobs g) {
   const GJob &J = g.j[blockIdx.y];
   if (blockIdx.x >= J.nblk) return;
@@ -439,119 +420,6 @@ hipError_t launch_resid_spec(int nx, int ny, int nz, const double *f, const doub
   }
 }
 
-template <typename T>
-hipError_t launch_yfwd(int nx, int ny, int nz, T *data, size_t sp, const cplx<double> *tw,
-                       const cplx<double> *ctw, int yw, hipStream_t st, bool xr, int shape,
-                       const PlaneMean &pm) {
-  if (yw == 3) {
-    // a field on the y faces: one FFT of twice the rows per column
-    if (shape != 0) return hipErrorInvalidValue;
-    switch (2 * ny) {
-#define PF_CASE(N)                                                                            \
-  case N: {                                                                                   \
-    constexpr int TPL = y_tpl(N), LPW = y_lpw<T>(N);                                          \
-    if (nx % (2 * LPW)) return hipErrorInvalidValue;                                          \
-    const int nib = nx / (2 * LPW);                                                           \
-    hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 3>), dim3((unsigned)((long)nib * nz)),          \
-                       dim3(TPL * LPW), 0, st, data, tw, ctw, nx, nib, sp, PlaneMean{});      \
-    return hipGetLastError();                                                                 \
-  }
-      PF_FOR_FFT_SIZES_Y(PF_CASE)
-#undef PF_CASE
-      default:
-        return hipErrorInvalidValue;
-    }
-  }
-  if (shape != 0) {
-    if (yw != 0 || xr) return hipErrorInvalidValue;
-    if (shape == kYPersistShape) return launch_y_persist<T>(false, nx, ny, nz, data, sp, tw, st, pm);
-    return launch_y_alt<T>(false, shape, nx, ny, nz, data, sp, tw, st, pm);
-  }
-  switch (ny) {
-#define PF_CASE(N)                                                                            \
-  case N: {                                                                                   \
-    constexpr int TPL = y_tpl(N), LPW = y_lpw<T>(N);                                          \
-    if (nx % (2 * LPW)) return hipErrorInvalidValue;                                          \
-    const int nib = nx / (2 * LPW);                                                           \
-    const dim3 g((unsigned)((long)nib * nz)), b(TPL * LPW);                                   \
-    if (yw != 0 && !ctw) return hipErrorInvalidValue;                                         \
-    if (yw == 1)                                                                              \
-      hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 1>), g, b, 0, st, data, tw, ctw, nx, nib,    \
-                         sp, pm);                                                             \
-    else if (yw == 2)                                                                         \
-      hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 2>), g, b, 0, st, data, tw, ctw, nx, nib,    \
-                         sp, pm);                                                             \
-    else if (xr)                                                                              \
-      hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 0, true>), g, b, 0, st, data, tw, ctw, nx,   \
-                         nib, sp, pm);                                                        \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, 0>), g, b, 0, st, data, tw, ctw, nx, nib,    \
-                         sp, pm);                                                               \
-    return hipGetLastError();                                                                 \
-  }
-    PF_FOR_FFT_SIZES_Y(PF_CASE)
-#undef PF_CASE
-    default:
-      return hipErrorInvalidValue;
-  }
-}
-
-template <typename T>
-hipError_t launch_yinv(int nx, int ny, int nz, T *data, size_t sp, const cplx<double> *tw,
-                       const cplx<double> *ctw, int yw, hipStream_t st, bool xr, int shape) {
-  if (yw == 3) {
-    // a field on the y faces: one FFT of twice the rows per column
-    if (shape != 0) return hipErrorInvalidValue;
-    switch (2 * ny) {
-#define PF_CASE(N)                                                                            \
-  case N: {                                                                                   \
-    constexpr int TPL = y_tpl(N), LPW = y_lpw<T>(N);                                          \
-    if (nx % (2 * LPW)) return hipErrorInvalidValue;                                          \
-    const int nib = nx / (2 * LPW);                                                           \
-    hipLaunchKernelGGL((k_yinv<T, N, TPL, LPW, 3>), dim3((unsigned)((long)nib * nz)),          \
-                       dim3(TPL * LPW), 0, st, data, tw, ctw, nx, nib, sp);                   \
-    return hipGetLastError();                                                                 \
-  }
-      PF_FOR_FFT_SIZES_Y(PF_CASE)
-#undef PF_CASE
-      default:
-        return hipErrorInvalidValue;
-    }
-  }
-  if (shape != 0) {
-    if (yw != 0 || xr) return hipErrorInvalidValue;
-    if (shape == kYPersistShape) return launch_y_persist<T>(true, nx, ny, nz, data, sp, tw, st);
-    return launch_y_alt<T>(true, shape, nx, ny, nz, data, sp, tw, st);
-  }
-  switch (ny) {
-#define PF_CASE(N)                                                                            \
-  case N: {                                                                                   \
-    constexpr int TPL = y_tpl(N), LPW = y_lpw<T>(N);                                          \
-    if (nx % (2 * LPW)) return hipErrorInvalidValue;                                          \
-    const int nib = nx / (2 * LPW);                                                           \
-    const dim3 g((unsigned)((long)nib * nz)), b(TPL * LPW);                                   \
-    if (yw != 0 && !ctw) return hipErrorInvalidValue;                                         \
-    if (yw == 1)                                                                              \
-      hipLaunchKernelGGL((k_yinv<T, N, TPL, LPW, 1>), g, b, 0, st, data, tw, ctw, nx, nib,    \
-                         sp);                                                                 \
-    else if (yw == 2)                                                                         \
-      hipLaunchKernelGGL((k_yinv<T, N, TPL, LPW, 2>), g, b, 0, st, data, tw, ctw, nx, nib,    \
-                         sp);                                                                 \
-    else if (xr)                                                                              \
-      hipLaunchKernelGGL((k_yinv<T, N, TPL, LPW, 0, true>), g, b, 0, st, data, tw, ctw, nx,   \
-                         nib, sp);                                                            \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_yinv<T, N, TPL, LPW, 0>), g, b, 0, st, data, tw, ctw, nx, nib,    \
-                         sp);                                                                 \
-    return hipGetLastError();                                                                 \
-  }
-    PF_FOR_FFT_SIZES_Y(PF_CASE)
-#undef PF_CASE
-    default:
-      return hipErrorInvalidValue;
-  }
-}
-
 template <typename TS, typename TO>
 hipError_t launch_xinv(int nx, int ny, const TS *in, size_t sp, TO *out, const cplx<double> *tw,
                        const double *zm, const TS *in2, double scale, long lines,
@@ -616,15 +484,6 @@ hipError_t launch_xinv(int nx, int ny, const TS *in, size_t sp, TO *out, const c
   }
 }
 
-// grouped launchers: the grid spans the widest job; every job of a group
-// has the length of the switch
-static dim3 grp_grid(const GJobs &g) {
-  unsigned m = 1;
-  for (int k = 0; k < g.count; ++k) m = g.j[k].nblk > m ? g.j[k].nblk : m;
-  return dim3(m, (unsigned)g.count);
-}
-static bool grp_ok(const GJobs &g) { return g.count >= 1 && g.count <= kMaxGroupJobs; }
-
 hipError_t launch_xfwd_grp(int nx, GJobs &g, hipStream_t st) {
   if (!grp_ok(g)) return hipErrorInvalidValue;
   switch (nx) {
@@ -644,32 +503,6 @@ hipError_t launch_xfwd_grp(int nx, GJobs &g, hipStream_t st) {
       return hipErrorInvalidValue;
   }
 }
-
-template <bool INV>
-static hipError_t launch_y_grp(int ny, GJobs &g, hipStream_t st) {
-  if (!grp_ok(g)) return hipErrorInvalidValue;
-  switch (ny) {
-#define PF_CASE(N)                                                                            \
-  case N: {                                                                                   \
-    constexpr int TPL = y_tpl(N), LPW = y_lpw<float>(N);                                      \
-    for (int k = 0; k < g.count; ++k) {                                                       \
-      if (g.j[k].ny != N || g.j[k].nx % (2 * LPW)) return hipErrorInvalidValue;               \
-      g.j[k].nblk = (unsigned)(g.j[k].nx / (2 * LPW) * g.j[k].nz);                            \
-    }                                                                                         \
-    if (INV)                                                                                  \
-      hipLaunchKernelGGL((k_yinv_grp<N, TPL, LPW>), grp_grid(g), dim3(TPL * LPW), 0, st, g);  \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_yfwd_grp<N, TPL, LPW>), grp_grid(g), dim3(TPL * LPW), 0, st, g);  \
-    return hipGetLastError();                                                                 \
-  }
-    PF_FOR_FFT_SIZES_Y(PF_CASE)
-#undef PF_CASE
-    default:
-      return hipErrorInvalidValue;
-  }
-}
-hipError_t launch_yfwd_grp(int ny, GJobs &g, hipStream_t st) { return launch_y_grp<false>(ny, g, st); }
-hipError_t launch_yinv_grp(int ny, GJobs &g, hipStream_t st) { return launch_y_grp<true>(ny, g, st); }
 
 hipError_t launch_resid_grp(int nx, GJobs &g, hipStream_t st) {
   if (!grp_ok(g)) return hipErrorInvalidValue;
@@ -717,14 +550,6 @@ template hipError_t launch_xfwd<double>(int, int, const double *, double *, size
 template hipError_t launch_xfwd<float>(int, int, const double *, float *, size_t,
                                        const cplx<double> *, double *, long, hipStream_t, int,
                                        const cplx<double> *, int);
-template hipError_t launch_yfwd<double>(int, int, int, double *, size_t, const cplx<double> *,
-                                        const cplx<double> *, int, hipStream_t, bool, int, const PlaneMean &);
-template hipError_t launch_yfwd<float>(int, int, int, float *, size_t, const cplx<double> *,
-                                        const cplx<double> *, int, hipStream_t, bool, int, const PlaneMean &);
-template hipError_t launch_yinv<double>(int, int, int, double *, size_t, const cplx<double> *,
-                                        const cplx<double> *, int, hipStream_t, bool, int);
-template hipError_t launch_yinv<float>(int, int, int, float *, size_t, const cplx<double> *,
-                                       const cplx<double> *, int, hipStream_t, bool, int);
 template hipError_t launch_xinv<double, double>(int, int, const double *, size_t, double *,
                                                 const cplx<double> *, const double *,
                                                 const double *, double, long, hipStream_t,

@@ -3,7 +3,7 @@
 // per workgroup, radix order), for the lengths 256, 512, 1024 and 2048. The
 // kernels are the templates of fft_kernels.hpp; the default shapes are
 // instantiated in kernels_fft.hip only.
-#include "fft_kernels.hpp"
+#include "fft_y.hpp"
 #include "pf_internal.hpp"
 
 namespace pf {
@@ -48,6 +48,14 @@ hipError_t y_one(bool inv, int nx, int nz, T *data, size_t sp, const cplx<double
   if constexpr (h.ok) {
     if (nx % (2 * h.lpw)) return hipErrorInvalidValue;
     const int nib = nx / (2 * h.lpw);
+    if constexpr (y_in_regs<T>(N) && S != 3) {
+      const dim3 gr((unsigned)((long)nib * nz)), br(LinePlan<N>::tpl * h.lpw);
+      if (inv)
+        hipLaunchKernelGGL((k_yr<T, N, h.lpw, true, 0, false>), gr, br, 0, st, data, tw, nullptr, nx, nib, sp, pm);
+      else
+        hipLaunchKernelGGL((k_yr<T, N, h.lpw, false, 0, false>), gr, br, 0, st, data, tw, nullptr, nx, nib, sp, pm);
+      return hipGetLastError();
+    } else {
     const dim3 g((unsigned)((long)nib * nz)), b(h.tpl * h.lpw);
     if (inv)
       hipLaunchKernelGGL((k_yinv<T, N, h.tpl, h.lpw, 0, false, h.ro>), g, b, 0, st, data, tw, nullptr, nx, nib,
@@ -56,6 +64,7 @@ hipError_t y_one(bool inv, int nx, int nz, T *data, size_t sp, const cplx<double
       hipLaunchKernelGGL((k_yfwd<T, N, h.tpl, h.lpw, 0, false, h.ro>), g, b, 0, st, data, tw, nullptr, nx, nib,
                          sp, pm);
     return hipGetLastError();
+    }
   } else {
     return hipErrorInvalidValue;
   }

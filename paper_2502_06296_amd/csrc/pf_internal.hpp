@@ -98,6 +98,28 @@ constexpr int y_lpw(int n) {
   return v;
 }
 
+// The y transforms of the register engine (fft_regs.hpp, fft_y.hpp): the
+// lengths it takes (the LDS engine keeps the shorter ones, where it is as
+// fast: 512 float64 points 0.75 against 0.78 ms at 1024 x 512 x 512; from 192
+// float32 and 768 float64 points on the register engine is ahead, 1024
+// float32 points 0.90 against 1.37 ms at 1024 x 1024 x 512), and its lines per
+// workgroup, 2 LPW contiguous values of every row: 128 bytes where
+// about 100 KB of LDS hold the lines (8 bytes a point). Fewer lines in two
+// workgroups of a compute unit are slower: 3072 float32 points 0.97 ms with
+// 4 lines in one workgroup, 1.43 ms with 2 lines in two.
+template <typename T>
+constexpr bool y_in_regs(int n) {
+  return n >= (sizeof(T) == 8 ? 768 : 192);
+}
+template <typename T>
+constexpr int yr_lpw(int n) {
+  const int want = sizeof(T) == 8 ? 8 : 16;
+  const int fit = 13900 / n;
+  int v = 2;
+  while (v * 2 <= want && v * 2 <= fit) v *= 2;
+  return v;
+}
+
 // Launch shapes of the periodic transforms the autotuner chooses from, per
 // family: 0 the default above; 1 half the threads per line (twice the
 // values per thread); 2 twice the threads per line (x transforms and the
@@ -106,10 +128,12 @@ constexpr int y_lpw(int n) {
 // lengths 256, 512, 1024 and 2048 where the length, the 1024-thread and the
 // LDS limits allow them; shapes 0-2 compute the same butterflies (up to the
 // compiler's fusion of multiply-adds), shape 3 in a different order of
-// passes.
+// passes. Where the default y transform is the register engine's, shape 1 is
+// half its lines per workgroup, shape 2 twice them (up to 16) and shape 3 the
+// LDS engine's.
 // Shape 4 (y transforms only, every length): the default threads and lines
-// in a persistent launch that prefetches each workgroup's next block
-// (k_y_persist).
+// in a persistent launch; on the LDS engine it prefetches each workgroup's
+// next block (k_y_persist).
 constexpr int kTransformShapes = 5;
 constexpr int kYPersistShape = 4;
 constexpr bool tuned_len(int n) { return n == 256 || n == 512 || n == 1024 || n == 2048; }
@@ -132,6 +156,11 @@ constexpr TShape xinv_shape(int n, int s) { return alt_shape(n, s, x_tpl(n), x_l
 constexpr TShape resid_shape(int n, int s) { return alt_shape(n, s, resid_tpl(n), resid_lpw(n), false, 0, 16); }
 template <typename T>
 constexpr TShape y_shape(int n, int s) {
+  if (y_in_regs<T>(n) && tuned_len(n)) {
+    const int l = yr_lpw<T>(n);
+    if (s == 1) return {0, l / 2, 0, true};
+    if (s == 2) return {0, 2 * l <= 16 ? 2 * l : l, 0, n > 256};
+  }
   return alt_shape(n, s, y_tpl(n), y_lpw<T>(n), true, y_stride(n) * 16, 8);
 }
 
@@ -314,6 +343,13 @@ struct GJobs {
   GJob j[kMaxGroupJobs];
   int count;
 };
+// the grid of a grouped launch spans its widest job
+inline dim3 grp_grid(const GJobs &g) {
+  unsigned m = 1;
+  for (int k = 0; k < g.count; ++k) m = g.j[k].nblk > m ? g.j[k].nblk : m;
+  return dim3(m, (unsigned)g.count);
+}
+inline bool grp_ok(const GJobs &g) { return g.count >= 1 && g.count <= kMaxGroupJobs; }
 hipError_t launch_xfwd_grp(int nx, GJobs &g, hipStream_t st);
 hipError_t launch_yfwd_grp(int ny, GJobs &g, hipStream_t st);
 hipError_t launch_yinv_grp(int ny, GJobs &g, hipStream_t st);
