@@ -8,19 +8,6 @@
 namespace pf {
 
 namespace {
-// compute units of the current device
-int device_cus() {
-  static int cached[64] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  if (!cached[dev]) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) return 0;
-    cached[dev] = n;
-  }
-  return cached[dev];
-}
-
 template <typename T, int N, bool INV>
 hipError_t y_persist_one(int nx, int nz, T *data, size_t sp, const cplx<double> *tw, hipStream_t st,
                          const PlaneMean &pm) {

@@ -487,6 +487,144 @@ __global__ __launch_bounds__(512, WAVES) void k_zsolve2(TS *data, int nx, int ny
 // reduction alternate between the two sets: a step writes one set while the
 // previous step's reads of the other may still be in flight, so a step
 // takes one barrier instead of two.
+// Hides a per-lane column pointer from common-subexpression elimination:
+// with chunks narrower than a wave the row addresses are per-lane 64-bit
+// values, and keeping all of them from the loads to the stores of a sweep
+// took as many registers as the column itself; they are recomputed instead.
+template <typename TS>
+__device__ __forceinline__ TS *fresh(TS *p) {
+  uintptr_t a = reinterpret_cast<uintptr_t>(p);
+  asm volatile("" : "+v"(a));
+  // as a global address: through a plain integer the accesses become flat
+  // ones, whose waits are the LDS accesses' too
+  return (TS *)(TS __attribute__((address_space(1))) *)a;
+}
+
+// One column pair's solve in separator form, in place on the right-hand sides
+// d0, d1 (negated) of the thread's chunk. tag / agc / exc: the z tables in LDS
+// (of the workgroup, and from the chunk's rows on); X1: the reduced-row
+// arrays, three of [P][TP], six with DB.
+// PS: chunks the arrays are laid out for, a constant that saves the address
+// registers of a run-time count (0: P).
+template <int M, int TP, int NR, bool DB, bool kFence, int PS = 0>
+__device__ __forceinline__ void sep_solve(double (&d0)[M], double (&d1)[M], double lam, const cplx<double> *tag,
+                                          const cplx<double> *agc, const double *exc, cplx<double> *X1,
+                                          int P, int ch, int pc) {
+  using D2 = cplx<double>;
+  const int ps = PS ? PS : P;
+  auto al = [&](int q) { return agc[q * ps].x; };
+  auto ga = [&](int q) { return agc[q * ps].y; };
+  auto ex = [&](int q) { return exc[q * ps]; };
+  D2 *const X2 = X1 + ps * TP, *const X3 = X2 + ps * TP;
+  const int me = ch * TP + pc;
+  const int nch = ch + 1 < P ? ch + 1 : ch;  // the last chunk's gamma is 0
+  const int nb = nch * TP + pc;
+  double ib_[M];
+  // upward sweep over the interior: the chunk's first row in terms of the
+  // previous separator (alpha_0) and the own separator (ug)
+  {
+    double ug = ga(M - 2), ue = ex(M - 2) + lam, u0 = d0[M - 2], u1 = d1[M - 2];
+    double cb = al(M - 2) + ug + ue;
+#pragma unroll
+    for (int q = M - 3; q >= 0; --q) {
+      const double t = ga(q) * rcpn<NR>(cb);
+      ug = t * ug;
+      ue = (ex(q) + lam) + t * ue;
+      u0 = d0[q] + t * u0;
+      u1 = d1[q] + t * u1;
+      cb = al(q) + ug + ue;
+      if constexpr (kFence) sched_fence(q);
+    }
+    X1[me] = mkc<double>(ug, ue);
+    X2[me] = mkc<double>(u0, u1);
+  }
+  // downward sweep from the first row (coupled to the previous separator)
+  double fa = al(0), fe = ex(0) + lam;
+  ib_[0] = rcpn<NR>(fa + ga(0) + fe);
+#pragma unroll
+  for (int q = 1; q < M; ++q) {
+    const double t = al(q) * ib_[q - 1];
+    fa = t * fa;
+    fe = (ex(q) + lam) + t * fe;
+    d0[q] = d0[q] + t * d0[q - 1];
+    d1[q] = d1[q] + t * d1[q - 1];
+    if (q < M - 1) ib_[q] = rcpn<NR>(fa + ga(q) + fe);
+    if constexpr (kFence) sched_fence(q);
+  }
+  __syncthreads();
+  double A, G, E, S0, S1;
+  {
+    const D2 gu = X1[nb], uu = X2[nb];
+    const double t = ga(M - 1) * rcpn<NR>(tag[nch].x + gu.x + gu.y);
+    const double sa = fa, sg = t * gu.x, se = fe + t * gu.y;
+    const double s0 = d0[M - 1] + t * uu.x, s1 = d1[M - 1] + t * uu.y;
+    const double b = rcpn<NR>(sa + sg + se);
+    A = sa * b; G = sg * b; E = se * b; S0 = s0 * b; S1 = s1 * b;
+  }
+  __syncthreads();
+  // cyclic reduction on the P separator rows (normalised, see k_zsolve2)
+  D2 *F2 = X2;  // the set the separator values go to
+  if constexpr (DB) {
+    D2 *const Y1 = X3 + ps * TP, *const Y2 = Y1 + ps * TP, *const Y3 = Y2 + ps * TP;
+    bool odd = false;
+    for (int s = 1; s < P; s *= 2) {
+      D2 *const Z1 = odd ? Y1 : X1, *const Z2 = odd ? Y2 : X2, *const Z3 = odd ? Y3 : X3;
+      Z1[me] = mkc<double>(A, E);
+      Z2[me] = mkc<double>(S0, S1);
+      Z3[me] = mkc<double>(G, E);
+      __syncthreads();
+      const int lo = (ch - s < 0 ? 0 : ch - s) * TP + pc;
+      const int hi = (ch + s >= P ? P - 1 : ch + s) * TP + pc;
+      const D2 ae = Z1[lo], dl = Z2[lo], ge = Z3[hi], dh = Z2[hi];
+      const double na = A * ae.x, ng = G * ge.x, ne = E + A * ae.y + G * ge.y;
+      const double n0 = S0 + A * dl.x + G * dh.x, n1 = S1 + A * dl.y + G * dh.y;
+      const double b = rcpn<NR>(na + ng + ne);
+      A = na * b; G = ng * b; E = ne * b; S0 = n0 * b; S1 = n1 * b;
+      odd = !odd;
+    }
+    // the set the last step did not read
+    F2 = odd ? Y2 : X2;
+  } else {
+    for (int s = 1; s < P; s *= 2) {
+      X1[me] = mkc<double>(A, E);
+      X2[me] = mkc<double>(S0, S1);
+      X3[me] = mkc<double>(G, E);
+      __syncthreads();
+      const int lo = (ch - s < 0 ? 0 : ch - s) * TP + pc;
+      const int hi = (ch + s >= P ? P - 1 : ch + s) * TP + pc;
+      const D2 ae = X1[lo], dl = X2[lo], ge = X3[hi], dh = X2[hi];
+      const double na = A * ae.x, ng = G * ge.x, ne = E + A * ae.y + G * ge.y;
+      const double n0 = S0 + A * dl.x + G * dh.x, n1 = S1 + A * dl.y + G * dh.y;
+      __syncthreads();
+      const double b = rcpn<NR>(na + ng + ne);
+      A = na * b; G = ng * b; E = ne * b; S0 = n0 * b; S1 = n1 * b;
+    }
+  }
+  // separator values: the own one and the previous chunk's
+  F2[me] = mkc<double>(S0, S1);
+  __syncthreads();
+  const D2 xl = ch > 0 ? F2[me - TP] : mkc<double>(0.0, 0.0);
+  __syncthreads();
+  // interior: forward y_q = (D_q + fa_q x_lo) / b_q, backward x_q = y_q + gamma_q x_{q+1} / b_q
+  double a = al(0);
+#pragma unroll
+  for (int q = 0; q < M - 1; ++q) {
+    if (q >= 1) a = al(q) * ib_[q - 1] * a;
+    d0[q] = (d0[q] + a * xl.x) * ib_[q];
+    d1[q] = (d1[q] + a * xl.y) * ib_[q];
+    if constexpr (kFence) sched_fence(q);
+  }
+  d0[M - 1] = S0;
+  d1[M - 1] = S1;
+#pragma unroll
+  for (int q = M - 2; q >= 0; --q) {
+    const double c = ga(q) * ib_[q];
+    d0[q] = d0[q] + c * d0[q + 1];
+    d1[q] = d1[q] + c * d1[q + 1];
+    if constexpr (kFence) sched_fence(q);
+  }
+}
+
 template <typename TS, int M, int TP, int NR, int WAVES, int MAXT = 512, bool TILE = false, int R = 1,
           bool DB = false>
 __device__ __forceinline__ void zsolve3_body(TS *data, int nx, int ny, int nz, int P,
@@ -517,8 +655,6 @@ __device__ __forceinline__ void zsolve3_body(TS *data, int nx, int ny, int nz, i
                              : (size_t)NX * P * TP * sizeof(D2)) / sizeof(double);
   double *const reg0 = tex + P * M;
   D2 *X1 = reinterpret_cast<D2 *>(reg0);
-  D2 *X2 = X1 + P * TP;
-  D2 *X3 = X2 + P * TP;
   TS *tile = reinterpret_cast<TS *>(reg0);
   const int nib = nx / (R * TC);
   const int blk = (int)xcd_block(bx_, gx_);
@@ -533,12 +669,6 @@ __device__ __forceinline__ void zsolve3_body(TS *data, int nx, int ny, int nz, i
   const size_t vplane = plane / 2;
   const D2 *agc = tag + ch;
   const double *exc = tex + ch;
-  auto al = [&](int q) { return agc[q * P].x; };
-  auto ga = [&](int q) { return agc[q * P].y; };
-  auto ex = [&](int q) { return exc[q * P]; };
-  const int me = ch * TP + pc;
-  const int nch = ch + 1 < P ? ch + 1 : ch;  // the last chunk's gamma is 0
-  const int nb = nch * TP + pc;
   const int npass = ib == 0 || xr ? 2 : 1;  // uniform per workgroup
   // 16-byte vectors of a round's row segment and of a tile row, and the
   // tile's first row in global memory
@@ -576,7 +706,7 @@ __device__ __forceinline__ void zsolve3_body(TS *data, int nx, int ny, int nz, i
     const bool st1 = xr ? pass == 1
                         : (pass == 0 && (npass == 1 || i != 0)) || (pass == 1 && i == 0);
 
-    double d0[M], d1[M], ib_[M];
+    double d0[M], d1[M];
     // the 1024-thread shapes have half the registers: compiler fences keep
     // their unrolled sweeps from issuing every read up front
     constexpr bool kFence = MAXT > 512 || M >= 32;
@@ -590,109 +720,7 @@ __device__ __forceinline__ void zsolve3_body(TS *data, int nx, int ny, int nz, i
     }
     // every thread holds its rows before the reduced-row arrays reuse the tile
     if constexpr (TL) __syncthreads();
-    // upward sweep over the interior: the chunk's first row in terms of the
-    // previous separator (alpha_0) and the own separator (ug)
-    {
-      double ug = ga(M - 2), ue = ex(M - 2) + lam, u0 = d0[M - 2], u1 = d1[M - 2];
-      double cb = al(M - 2) + ug + ue;
-#pragma unroll
-      for (int q = M - 3; q >= 0; --q) {
-        const double t = ga(q) * rcpn<NR>(cb);
-        ug = t * ug;
-        ue = (ex(q) + lam) + t * ue;
-        u0 = d0[q] + t * u0;
-        u1 = d1[q] + t * u1;
-        cb = al(q) + ug + ue;
-        if constexpr (kFence) sched_fence(q);
-      }
-      X1[me] = mkc<double>(ug, ue);
-      X2[me] = mkc<double>(u0, u1);
-    }
-    // downward sweep from the first row (coupled to the previous separator)
-    double fa = al(0), fe = ex(0) + lam;
-    ib_[0] = rcpn<NR>(fa + ga(0) + fe);
-#pragma unroll
-    for (int q = 1; q < M; ++q) {
-      const double t = al(q) * ib_[q - 1];
-      fa = t * fa;
-      fe = (ex(q) + lam) + t * fe;
-      d0[q] = d0[q] + t * d0[q - 1];
-      d1[q] = d1[q] + t * d1[q - 1];
-      if (q < M - 1) ib_[q] = rcpn<NR>(fa + ga(q) + fe);
-      if constexpr (kFence) sched_fence(q);
-    }
-    __syncthreads();
-    double A, G, E, S0, S1;
-    {
-      const D2 gu = X1[nb], uu = X2[nb];
-      const double t = ga(M - 1) * rcpn<NR>(tag[nch].x + gu.x + gu.y);
-      const double sa = fa, sg = t * gu.x, se = fe + t * gu.y;
-      const double s0 = d0[M - 1] + t * uu.x, s1 = d1[M - 1] + t * uu.y;
-      const double b = rcpn<NR>(sa + sg + se);
-      A = sa * b; G = sg * b; E = se * b; S0 = s0 * b; S1 = s1 * b;
-    }
-    __syncthreads();
-    // cyclic reduction on the P separator rows (normalised, see k_zsolve2)
-    D2 *F2 = X2;  // the set the separator values go to
-    if constexpr (DB) {
-      D2 *const Y1 = X3 + P * TP, *const Y2 = Y1 + P * TP, *const Y3 = Y2 + P * TP;
-      bool odd = false;
-      for (int s = 1; s < P; s *= 2) {
-        D2 *const Z1 = odd ? Y1 : X1, *const Z2 = odd ? Y2 : X2, *const Z3 = odd ? Y3 : X3;
-        Z1[me] = mkc<double>(A, E);
-        Z2[me] = mkc<double>(S0, S1);
-        Z3[me] = mkc<double>(G, E);
-        __syncthreads();
-        const int lo = (ch - s < 0 ? 0 : ch - s) * TP + pc;
-        const int hi = (ch + s >= P ? P - 1 : ch + s) * TP + pc;
-        const D2 ae = Z1[lo], dl = Z2[lo], ge = Z3[hi], dh = Z2[hi];
-        const double na = A * ae.x, ng = G * ge.x, ne = E + A * ae.y + G * ge.y;
-        const double n0 = S0 + A * dl.x + G * dh.x, n1 = S1 + A * dl.y + G * dh.y;
-        const double b = rcpn<NR>(na + ng + ne);
-        A = na * b; G = ng * b; E = ne * b; S0 = n0 * b; S1 = n1 * b;
-        odd = !odd;
-      }
-      // the set the last step did not read
-      F2 = odd ? Y2 : X2;
-    } else {
-      for (int s = 1; s < P; s *= 2) {
-        X1[me] = mkc<double>(A, E);
-        X2[me] = mkc<double>(S0, S1);
-        X3[me] = mkc<double>(G, E);
-        __syncthreads();
-        const int lo = (ch - s < 0 ? 0 : ch - s) * TP + pc;
-        const int hi = (ch + s >= P ? P - 1 : ch + s) * TP + pc;
-        const D2 ae = X1[lo], dl = X2[lo], ge = X3[hi], dh = X2[hi];
-        const double na = A * ae.x, ng = G * ge.x, ne = E + A * ae.y + G * ge.y;
-        const double n0 = S0 + A * dl.x + G * dh.x, n1 = S1 + A * dl.y + G * dh.y;
-        __syncthreads();
-        const double b = rcpn<NR>(na + ng + ne);
-        A = na * b; G = ng * b; E = ne * b; S0 = n0 * b; S1 = n1 * b;
-      }
-    }
-    // separator values: the own one and the previous chunk's
-    F2[me] = mkc<double>(S0, S1);
-    __syncthreads();
-    const D2 xl = ch > 0 ? F2[me - TP] : mkc<double>(0.0, 0.0);
-    __syncthreads();
-    // interior: forward y_q = (D_q + fa_q x_lo) / b_q, backward x_q = y_q + gamma_q x_{q+1} / b_q
-    double a = al(0);
-#pragma unroll
-    for (int q = 0; q < M - 1; ++q) {
-      if (q >= 1) a = al(q) * ib_[q - 1] * a;
-      d0[q] = (d0[q] + a * xl.x) * ib_[q];
-      d1[q] = (d1[q] + a * xl.y) * ib_[q];
-      if constexpr (kFence) sched_fence(q);
-    }
-    d0[M - 1] = S0;
-    d1[M - 1] = S1;
-#pragma unroll
-    for (int q = M - 2; q >= 0; --q) {
-      const double c = ga(q) * ib_[q];
-      d0[q] = d0[q] + c * d0[q + 1];
-      d1[q] = d1[q] + c * d1[q + 1];
-      if constexpr (kFence) sched_fence(q);
-    }
+    sep_solve<M, TP, NR, DB, kFence>(d0, d1, lam, tag, agc, exc, X1, P, ch, pc);
     if constexpr (TL) {
       // single pass: both columns, into the round's region (its reduced-row
       // arrays are read by now); the tile goes out after the last round
@@ -726,8 +754,6 @@ __device__ __forceinline__ void zsolve3_body(TS *data, int nx, int ny, int nz, i
       i += 2 * TP;
       cp += TP;
       X1 = reinterpret_cast<D2 *>(reg0 + rd * region);
-      X2 = X1 + P * TP;
-      X3 = X2 + P * TP;
       tile = reinterpret_cast<TS *>(reg0 + rd * region);
     }
     if (tiled)
@@ -751,6 +777,150 @@ __global__ __launch_bounds__(MAXT, WAVES) void k_zsolve3(TS *data, int nx, int n
   }
   zsolve3_body<TS, M, TP, NR, WAVES, MAXT, TILE, R, DB>(data, nx, ny, nz, P, zal, zga, zex, sx, sy, sp, xr,
                                                         bx, gx);
+}
+
+// The separator form in persistent workgroups: one round of resident
+// workgroups walks the tiles of 2 TP columns, and each loads its next tile's
+// rows into registers before it solves the current one, so that those loads
+// travel during the elimination. The z tables are staged once per workgroup.
+// PS: chunks of a column at most.
+//
+// What bounds it: the elimination itself at 1024 rows (one workgroup of 128
+// chunks a compute unit; about 13 us a tile, some 4 each of float64
+// arithmetic and of LDS accesses), HBM for the short columns. Float32 ms on
+// MI355X against the best of the shapes that load, solve and store in turn:
+//   1024 x 512 x 1024  2.06 -> 1.40     512 x 512 x 256  0.153 -> 0.144
+//   1024 x 512 x 512   0.72 -> 0.57     256 x 256 x 96   0.0275 -> 0.0201
+//   3456 x 3072 x 30   0.67 -> 0.53 (4.8 TB/s)
+// In float64 the next tile's rows take 32 registers, which leaves 12 waves a
+// compute unit instead of 16: slower than the direct shapes (1024 x 512 x 512
+// 1.21 against 1.05 ms) except on small planes of short columns (64 x 64 x 64
+// 8.1 against 10 us).
+template <typename TS, int M, int TP, int PS>
+__device__ __forceinline__ void zsolve4_body(TS *data, int nx, int ny, int nz, int P, const double *zal,
+                                             const double *zga, const double *zex, const double *sx,
+                                             const double *sy, size_t sp, int xr, unsigned bx, unsigned G) {
+  using V = cplx<TS>;
+  using D2 = cplx<double>;
+  extern __shared__ double red[];
+  D2 *tag = reinterpret_cast<D2 *>(red);
+  double *tex = reinterpret_cast<double *>(tag + PS * M);
+  for (int e = threadIdx.x; e < P * M; e += blockDim.x) {
+    const int o = (e % M) * PS + e / M;
+    tag[o] = mkc<double>(zal[e], zga[e]);
+    tex[o] = zex[e];
+  }
+  D2 *X1 = reinterpret_cast<D2 *>(tex + PS * M);
+  const unsigned nib = nx / (2 * TP);
+  const int pc = threadIdx.x % TP, ch = threadIdx.x / TP, r0 = ch * M;
+  const size_t vplane = sp / 2;
+  // the tiles of first passes, then those of second passes (the pair of slots
+  // 0 and 1 in every row j; with x walls every pair, see zsolve3_body), which
+  // read and write columns of their own
+  const unsigned n1 = nib * ny, ntiles = n1 + (xr ? n1 : ny);
+  auto tile_of = [&](unsigned i) {
+    const unsigned b0 = i * G;
+    return b0 + G <= ntiles ? b0 + xcd_block(bx, G) : b0 + bx;
+  };
+  struct Tile {
+    int j, i, pass;
+  };
+  auto place = [&](unsigned t) {
+    const bool second = t >= n1;
+    const unsigned u = second ? t - n1 : t;
+    const unsigned ib = second && !xr ? 0 : u % nib;
+    return Tile{(int)(second && !xr ? u : u / nib), 2 * (int)(ib * TP + pc), second ? 1 : 0};
+  };
+  // Nothing may touch a value of the next tile before its turn, nor a load
+  // be issued in a branch: the wait for either would be a wait for them all.
+  // So the two parts of the shift are kept apart, and rows past nz read the
+  // last row.
+  V nxt[M];
+  double sxn, syn;
+  auto load = [&](unsigned t) {
+    const Tile p = place(t);
+    const int ci = p.i + p.pass;
+    sxn = sx[ci];
+    syn = sy[(ci >= 2 ? ny : 0) + p.j];
+    const V *c = fresh(reinterpret_cast<const V *>(data + (size_t)p.j * nx + p.i + (size_t)r0 * sp));
+    const int last = nz - 1 - r0;  // >= 0
+#pragma unroll
+    for (int q = 0; q < M; ++q) nxt[q] = c[(size_t)(q < last ? q : last) * vplane];
+  };
+  unsigned t = tile_of(0);
+  if (t >= ntiles) return;  // uniform
+  load(t);
+  __syncthreads();
+  for (unsigned it = 0;;) {
+    const Tile p = place(t);
+    double d0[M], d1[M];
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+      d0[q] = r0 + q < nz ? -(double)nxt[q].x : 0.0;
+      d1[q] = r0 + q < nz ? -(double)nxt[q].y : 0.0;
+    }
+    const double lam0 = sxn + syn;
+    const bool zero_col = lam0 == 0.0;  // Poisson's (0,0) only
+    const unsigned tn = tile_of(++it);
+    const bool more = tn < ntiles;  // uniform
+    // the rows are taken over before their registers are loaded again (left
+    // to itself the compiler converts them later, from copies whose making
+    // waits for the loads)
+#pragma unroll
+    for (int q = 0; q < M; ++q) asm volatile("" : "+v"(d0[q]), "+v"(d1[q]));
+    load(more ? tn : t);  // the last turn's values are not used
+    sep_solve<M, TP, 1, true, true, PS>(d0, d1, zero_col ? 1.0 : lam0, tag, tag + ch, tex + ch, X1, P, ch, pc);
+    // a first pass stores both columns, except column 1 of the slots 0 and 1
+    // (with x walls of every pair), which a second pass stores
+    V *cp = fresh(reinterpret_cast<V *>(data + (size_t)p.j * nx + p.i + (size_t)r0 * sp));
+    const bool own = xr || p.i == 0;
+    if (p.pass == 0 && !own) {
+#pragma unroll
+      for (int q = 0; q < M; ++q)
+        if (r0 + q < nz) cp[(size_t)q * vplane] = V{(TS)d0[q], (TS)d1[q]};
+    } else if (own) {
+      TS *e = reinterpret_cast<TS *>(cp) + p.pass;
+#pragma unroll
+      for (int q = 0; q < M; ++q)
+        if (r0 + q < nz) e[(size_t)q * sp] = (TS)(p.pass ? d1[q] : zero_col ? 0.0 : d0[q]);
+    }
+    if (!more) break;
+    t = tn;
+  }
+}
+
+// waves per SIMD the registers leave room for
+template <typename TS>
+constexpr int z4_waves() { return sizeof(TS) == 4 ? 4 : 3; }
+template <typename TS, int M, int TP, int PS>
+__global__ __launch_bounds__(PS *TP, z4_waves<TS>()) void k_zsolve4(TS *data, int nx, int ny, int nz, int P,
+                                                                    const double *zal, const double *zga,
+                                                                    const double *zex, const double *sx,
+                                                                    const double *sy, size_t sp, int xr,
+                                                                    ZeroJob zj) {
+  unsigned bx = blockIdx.x, G = gridDim.x;
+  if (zj.m) {  // the first workgroup takes the zero mode
+    if (bx == 0) return zero_solve(zj, zga, nz);
+    --bx;
+    --G;
+  }
+  zsolve4_body<TS, M, TP, PS>(data, nx, ny, nz, P, zal, zga, zex, sx, sy, sp, xr, bx, G);
+}
+// Several problems of one chunk count (see GJobs), float32 and periodic x;
+// J.nblk is the job's share of the resident workgroups.
+template <int M, int TP, int PS>
+__global__ __launch_bounds__(PS *TP, z4_waves<float>()) void k_zsolve4_grp(const GJobs g) {
+  const GJob &J = g.j[blockIdx.y];
+  unsigned bx = blockIdx.x;
+  if (J.in2) {  // the job's first workgroup takes its zero mode
+    if (bx == 0)
+      return zero_solve(ZeroJob{J.zm, J.aux, const_cast<double *>(static_cast<const double *>(J.in2))}, J.zga,
+                        J.nz);
+    --bx;
+  }
+  if (bx >= J.nblk) return;  // uniform per block
+  zsolve4_body<float, M, TP, PS>(static_cast<float *>(J.out), J.nx, J.ny, J.nz, J.P, J.zal, J.zga, J.zex, J.sx,
+                                 J.sy, J.sp, 0, bx, J.nblk);
 }
 
 // one z-solve shape for several problems with the same chunk count (see
@@ -787,6 +957,7 @@ struct ZVariant {
   bool tile = false; // separator form with the column tile staged through LDS
   int rounds = 1;    // tiled: the threads take the TI columns in rounds of TI/rounds
   bool dbl = false;  // separator form: double-buffered reduced rows, one barrier per reduction step
+  bool persist = false;  // persistent workgroups that load the next tile ahead (k_zsolve4)
 };
 static const ZVariant kZVariants[] = {
     {16, 16, 0, false, false, 2}, {16, 16, 4, true, false, 2}, {16, 16, 0, true, false, 2},
@@ -819,6 +990,9 @@ static const ZVariant kZVariants[] = {
     // the 512-thread defaults of 512-row columns with double-buffered reduced rows
     {8, 16, 1, true, true, 1, false, true, 512, true, 1, true},
     {16, 32, 0, true, true, 1, false, true, 512, false, 1, true},
+    // persistent: 16 columns a tile, and 32 for columns of up to 128 rows
+    {8, 16, 4, true, true, 1, false, true, 1024, false, 1, true, true},
+    {8, 32, 4, true, true, 1, false, true, 256, false, 1, true, true},
 };
 constexpr int kZVariantCount = sizeof(kZVariants) / sizeof(kZVariants[0]);
 
@@ -854,6 +1028,8 @@ bool zsolve_variant_fits(int v, int nx, int nz, int esize) {
   const ZVariant &z = kZVariants[v];
   const int P = (nz + z.M - 1) / z.M;
   const int threads = z.paired ? P * z.TI / 2 / z.rounds : P * z.TI;
+  // float64 persistent launches: up to 16 chunks of 16-column tiles
+  if (z.persist && esize == 8 && (P > 16 || z.TI != 16)) return false;
   // a tiled launch needs whole 16-byte vectors per round's row segment and
   // at least two chunks
   if (z.tile && (z.TI / z.rounds * esize % 16 != 0 || P < 2)) return false;
@@ -861,37 +1037,96 @@ bool zsolve_variant_fits(int v, int nx, int nz, int esize) {
          zsolve_lds(z, P, esize) <= (z.maxt > 512 || z.tile ? 160 * 1024 : 65536);
 }
 
-int zsolve_default_variant(int nx, int nz, bool fp64) {
-  // fastest measured on MI355X at 1024x512x512: float64 storage 40 (1.037
-  // ms: separator form, 16 rows, 32 columns, double-buffered reduced rows),
-  // 21 (1.050, the same with one set), 10 (1.11); float32 storage (padded
-  // planes) 39 (0.711 ms: separator form, 8 rows, 16-column tiles through
-  // LDS, double-buffered reduced rows), 35 (0.752, one set), 31, 18 (0.84:
-  // 8 rows, 8 columns, direct); the unpaired 4
-  // and 3 as fall-backs where the LDS or thread budget excludes the paired
-  // shapes. At 1024 rows float64 storage takes 38 (11.06 ms at
-  // 2048x1024x1024: 28 with double-buffered reduced rows; 28 11.30, 20
-  // 11.52, the tiled 31 12.8, 4 22.2) and float32 storage the tiled 37 (8.01
-  // ms: 16-column tiles, double-buffered reduced rows; 29 8.20, 31 8.38, 18
-  // 8.9). Short
-  // columns (few chunks) would leave those shapes with tiny workgroups, so
-  // the first fitting shape with at least 128 threads wins, widened by the
-  // 64- and 128-column shapes.
-  static const int f64[] = {40, 21, 10, 19, 38, 26, 25, 24, 23, 20, 8, 4, 3},
-                   f32[] = {39, 35, 37, 29, 31, 18, 19, 16, 13, 24, 23, 26, 25, 8, 4, 3};
-  const int *list = fp64 ? f64 : f32;
-  const int len = fp64 ? (int)(sizeof(f64) / sizeof(int)) : (int)(sizeof(f32) / sizeof(int));
+int zsolve_default_variant(int nx, int ny, int nz, bool fp64) {
+  // Float32 storage: the persistent shapes, 32-column tiles while a column has
+  // at most 16 chunks (3456 x 3072 x 30 0.53 against 0.80 ms with 16 columns;
+  // 256 x 256 x 192 0.039 against 0.033).
+  // Float64 at 1024x512x512: 40 (1.037 ms: separator form, 16 rows, 32
+  // columns, double-buffered reduced rows), 21 (1.050, the same with one set),
+  // 10 (1.11); at 1024 rows 38 (11.06 ms at 2048x1024x1024: 28 with
+  // double-buffered reduced rows; 28 11.30, 20 11.52, the tiled 31 12.8, 4
+  // 22.2). Planes of up to 131072 columns do not fill the chip with those
+  // shapes: 18 (8 rows, 8 columns: 256x256x384 0.078 against 0.106 ms,
+  // 512x256x193 0.071 against 0.078; at 512x512x128 0.123 against 0.110), and
+  // up to 65536 columns of 16 chunks the persistent 41 (64x64x64 8.1 against
+  // 10.5 us). Other short columns (few chunks) would leave the first shapes
+  // with tiny workgroups, so the first fitting shape with at least 128 threads
+  // wins, widened by the 64- and 128-column shapes; the unpaired 4 and 3 are
+  // fall-backs where the LDS or thread budget excludes the paired shapes.
+  static const int f64[] = {40, 21, 10, 19, 38, 26, 25, 24, 23, 20, 8, 4, 3}, f32[] = {42, 41};
+  const long cols = (long)nx * ny;
+  auto fits = [&](int v) { return zsolve_variant_fits(v, nx, nz, fp64 ? 8 : 4); };
+  if (!fp64) {
+    for (int v : f32)
+      if (fits(v)) return v;
+    return -1;
+  }
+  if (cols <= 65536 && fits(41)) return 41;
+  if (cols <= 131072 && nz > 64 && fits(18)) return 18;
   auto threads = [&](int v) {
     const ZVariant &z = kZVariants[v];
     const int P = (nz + z.M - 1) / z.M;
     return z.paired ? P * z.TI / 2 / z.rounds : P * z.TI;
   };
-  for (int k = 0; k < len; ++k)
-    if (zsolve_variant_fits(list[k], nx, nz, fp64 ? 8 : 4) && threads(list[k]) >= 128) return list[k];
-  for (int k = 0; k < len; ++k)
-    if (zsolve_variant_fits(list[k], nx, nz, fp64 ? 8 : 4)) return list[k];
+  for (int v : f64)
+    if (fits(v) && threads(v) >= 128) return v;
+  for (int v : f64)
+    if (fits(v)) return v;
   return -1;
 }
+
+// LDS of a persistent workgroup, and how many of them the device holds: 4 or
+// 3 waves a SIMD (the kernel's registers) and 160 KB a compute unit.
+template <int M, int TP, int PS>
+constexpr size_t z4_lds() { return (size_t)3 * PS * M * 8 + (size_t)6 * PS * TP * 16; }
+template <typename TS, int M, int TP, int PS>
+static long z4_resident(int P) {
+  const int waves = (P * TP + 63) / 64;
+  return std::max<long>(std::min<long>(4 * z4_waves<TS>() / waves, 160 * 1024 / z4_lds<M, TP, PS>()), 1) *
+         device_cus();
+}
+template <typename TS, int M, int TP, int PS>
+static hipError_t launch_z4(int nx, int ny, int nz, TS *data, size_t sp, const double *zal, const double *zga,
+                            const double *zex, const double *sx, const double *sy, bool xr, const ZeroJob &zj,
+                            hipStream_t st) {
+  const int P = (nz + M - 1) / M;
+  const unsigned n1 = (unsigned)((long)(nx / (2 * TP)) * ny), ntiles = n1 + (xr ? n1 : (unsigned)ny);
+  const long res = z4_resident<TS, M, TP, PS>(P);
+  if (P > PS || res < 1) return hipErrorInvalidValue;
+  const unsigned G = (unsigned)std::min<long>(ntiles, res);
+  hipLaunchKernelGGL((k_zsolve4<TS, M, TP, PS>), dim3(G + (zj.m ? 1 : 0)), dim3(P * TP), (z4_lds<M, TP, PS>()),
+                     st, data, nx, ny, nz, P, zal, zga, zex, sx, sy, sp, (int)xr, zj);
+  return hipGetLastError();
+}
+template <int M, int TP, int PS>
+static hipError_t launch_z4_grp(GJobs &g, int P, hipStream_t st) {
+  const long res = z4_resident<float, M, TP, PS>(P);
+  if (P > PS || res < 1) return hipErrorInvalidValue;
+  // each job's share of the resident workgroups, by its tiles
+  long total = 0;
+  for (int k = 0; k < g.count; ++k) total += (long)(g.j[k].nx / (2 * TP) + 1) * g.j[k].ny;
+  unsigned mb = 1;
+  for (int k = 0; k < g.count; ++k) {
+    GJob &J = g.j[k];
+    const long n = (long)(J.nx / (2 * TP) + 1) * J.ny;
+    J.nblk = (unsigned)std::min<long>(n, std::max<long>(1, (res * n + total - 1) / total));
+    mb = std::max(mb, J.nblk + (J.in2 ? 1 : 0));
+  }
+  hipLaunchKernelGGL((k_zsolve4_grp<M, TP, PS>), dim3(mb, (unsigned)g.count), dim3(P * TP), (z4_lds<M, TP, PS>()),
+                     st, g);
+  return hipGetLastError();
+}
+// the smallest layout that holds P chunks: F<M, TP, PS>
+#define PF_Z4_PICK(TI_, P_, CALL)   \
+  if (TI_ == 32) {                  \
+    if (P_ <= 4) CALL(16, 4);       \
+    if (P_ <= 8) CALL(16, 8);       \
+    CALL(16, 16);                   \
+  }                                 \
+  if (P_ <= 16) CALL(8, 16);        \
+  if (P_ <= 32) CALL(8, 32);        \
+  if (P_ <= 64) CALL(8, 64);        \
+  CALL(8, 128);
 
 template <typename TS>
 hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const double *zal,
@@ -901,9 +1136,19 @@ hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const doub
   if (!zsolve_variant_fits(variant, nx, nz, (int)sizeof(TS))) return hipErrorInvalidValue;
   const ZVariant &z = kZVariants[variant];
   const int P = (nz + z.M - 1) / z.M;
+  if (zj.m && !zero_fits(nz, z.paired ? P * z.TI / 2 / z.rounds : P * z.TI)) return hipErrorInvalidValue;
+  if (z.persist) {
+#define PF_CALL(TP_, PS_) \
+  return launch_z4<TS, 8, TP_, PS_>(nx, ny, nz, data, sp, zal, zga, zex, sx, sy, xr, zj, st)
+    if constexpr (sizeof(TS) == 8) {
+      PF_CALL(8, 16);
+    } else {
+      PF_Z4_PICK(z.TI, P, PF_CALL)
+    }
+#undef PF_CALL
+  }
   const size_t shm = zsolve_lds(z, P, (int)sizeof(TS));
   dim3 g((unsigned)((long)(nx / z.TI) * ny) + (zj.m ? 1 : 0)), b(z.paired ? P * z.TI / 2 / z.rounds : P * z.TI);
-  if (zj.m && !zero_fits(nz, (int)b.x)) return hipErrorInvalidValue;
 #define PF_ZV(ID, M_, TI_, W_, F_)                                                                \
   case ID:                                                                                        \
     hipLaunchKernelGGL((k_zsolve<TS, M_, TI_, W_, F_>), g, b, shm, st, data, nx, ny, nz, P, zal, \
@@ -1009,6 +1254,11 @@ hipError_t launch_zsolve_grp(int variant, GJobs &g, hipStream_t st) {
     if (J.in2 && (!J.zm || !J.aux || !zero_fits(J.nz, P * z.TI / 2 / z.rounds))) return hipErrorInvalidValue;
     const unsigned nb = J.nblk + (J.in2 ? 1 : 0);
     mb = nb > mb ? nb : mb;
+  }
+  if (z.persist) {
+#define PF_CALL(TP_, PS_) return launch_z4_grp<8, TP_, PS_>(g, P, st)
+    PF_Z4_PICK(z.TI, P, PF_CALL)
+#undef PF_CALL
   }
   const size_t shm = zsolve_lds(z, P, 4);
   const dim3 gr(mb, (unsigned)g.count), b(P * z.TI / 2 / z.rounds);
@@ -1212,17 +1462,6 @@ struct HelmArgs {
 // Steps 2-4 for the chunk of one lane (see k_helm), with the Step 1 rows
 // from RW sources (GRow or LRow) and the reduced system's multipliers from
 // constant memory.
-// Hides a per-lane column pointer from common-subexpression elimination:
-// with chunks narrower than a wave the row addresses are per-lane 64-bit
-// values, and keeping all of them from the loads to the stores of a sweep
-// took as many registers as the column itself; they are recomputed instead.
-template <typename TS>
-__device__ __forceinline__ TS *fresh(TS *p) {
-  uintptr_t a = reinterpret_cast<uintptr_t>(p);
-  asm volatile("" : "+v"(a));
-  return reinterpret_cast<TS *>(a);
-}
-
 // Rows of the float64 right-hand side that the refinement of a 32-row chunk
 // narrower than a wave parks in LDS (the rest stay in registers): all 32 in
 // registers spill, and reading them again from global memory doubled the

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 
@@ -27,6 +28,19 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
   X(3456)
 #define PF_FOR_FFT_SIZES(X) PF_FOR_FFT_SIZES_COMMON(X)
 #define PF_FOR_FFT_SIZES_Y(X) PF_FOR_FFT_SIZES_COMMON(X)
+
+// compute units of the current device (0 on error)
+inline int device_cus() {
+  static std::atomic<int> cached[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  int v = cached[dev].load(std::memory_order_relaxed);
+  if (!v) {
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) return 0;
+    cached[dev].store(v, std::memory_order_relaxed);
+  }
+  return v;
+}
 
 bool fft_size_supported(int n);    // x direction
 bool fft_size_supported_y(int n);  // y direction
@@ -304,7 +318,7 @@ hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const doub
                          int variant, hipStream_t st, bool xr = false, const ZeroJob &zj = ZeroJob{});
 int zsolve_variant_count();
 bool zsolve_variant_fits(int variant, int nx, int nz, int esize);  // esize: bytes per stored value
-int zsolve_default_variant(int nx, int nz, bool fp64);
+int zsolve_default_variant(int nx, int ny, int nz, bool fp64);
 
 // ----------------------------------------------------- grouped launches
 // One launch runs one stage of several independent problems that share the
