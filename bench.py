@@ -43,7 +43,8 @@ LX, LY, LZ = 2 * math.pi, math.pi, 2.0
 S_HELM = 0.5 * (1.0 / 5200.0) * 1e-4     # alpha * nu * dt, Re_tau = 5200
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_counters.json")
 KERNEL_SOURCES = ["paper_2502_06296_amd/csrc/kernels_fft.hip", "paper_2502_06296_amd/csrc/kernels_fft_y.hip",
-                  "paper_2502_06296_amd/csrc/fft_y.hpp", "paper_2502_06296_amd/csrc/fft_regs.hpp",
+                  "paper_2502_06296_amd/csrc/fft_y.hpp", "paper_2502_06296_amd/csrc/fft_x.hpp",
+                  "paper_2502_06296_amd/csrc/fft_regs.hpp",
                   "paper_2502_06296_amd/csrc/kernels_fft_alt.hip",
                   "paper_2502_06296_amd/csrc/kernels_fft_pf.hip", "paper_2502_06296_amd/csrc/kernels_z.hip",
                   "paper_2502_06296_amd/csrc/fft_kernels.hpp", "paper_2502_06296_amd/csrc/fft_lds.hpp",

@@ -97,8 +97,35 @@ PF_PLAN(PairPlan, 2048, 128, 16, 16, 8)
 PF_PLAN(PairPlan, 3072, 192, 16, 4, 6, 8)
 PF_PLAN(PairPlan, 3200, 200, 16, 5, 5, 8)
 PF_PLAN(PairPlan, 3456, 216, 16, 9, 3, 8)
+// The reverse: a first pass of radix 8 on the butterflies j and N/8 - j, for
+// inverses that unfold such a spectrum as they read it.
+template <int N> struct UnpairPlan;
+PF_PLAN(UnpairPlan, 192, 12, 8, 3, 8)
+PF_PLAN(UnpairPlan, 256, 16, 8, 4, 8)
+PF_PLAN(UnpairPlan, 384, 24, 8, 3, 16)
+PF_PLAN(UnpairPlan, 512, 32, 8, 4, 16)
+PF_PLAN(UnpairPlan, 768, 48, 8, 6, 16)
+PF_PLAN(UnpairPlan, 1024, 64, 8, 8, 16)
+PF_PLAN(UnpairPlan, 1536, 96, 8, 12, 16)
+PF_PLAN(UnpairPlan, 2048, 128, 8, 16, 16)
+PF_PLAN(UnpairPlan, 3072, 192, 8, 6, 4, 16)
+PF_PLAN(UnpairPlan, 3200, 200, 8, 5, 5, 16)
+PF_PLAN(UnpairPlan, 3456, 216, 8, 3, 9, 16)
 #undef PF_PLAN
 #define PF_FOR_LINE_PLANS(X) X(192) X(256) X(384) X(512) X(768) X(1024) X(1536) X(2048) X(3072) X(3200) X(3456)
+
+// threads of a line, 0 for a length without a plan
+constexpr int rx_tpl(int n) {
+  switch (n) {
+#define PF_CASE(N) \
+  case N:          \
+    return LinePlan<N>::tpl;
+    PF_FOR_LINE_PLANS(PF_CASE)
+#undef PF_CASE
+    default:
+      return 0;
+  }
+}
 
 // v[r] times W^(e r), from one table read W^e (two, W^(4e) too, from radix 8
 // on): the powers r = 4 m + d as products of W^(4 m) and W^d, made where they
@@ -137,11 +164,13 @@ __host__ __device__ constexpr int rx_stride(int n, int lpw) {
 }
 
 // Butterfly `it` of thread t in pass I: t + it TPL, or in the last pass of a
-// PAIR transform the butterflies m and NB - m (0 and NB/2 for m = 0).
-template <class P, int I, bool PAIR>
+// kPair transform (the first of a kUnpair one) the butterflies t and NB - t
+// (0 and NB/2 for t = 0).
+enum : int { kPlain = 0, kPair = 1, kUnpair = 2 };
+template <class P, int I, int PAIR>
 __device__ __forceinline__ int rx_butterfly(int t, int it) {
   constexpr int NB = P::n / P::radix[I];
-  if constexpr (PAIR && I + 1 == P::passes) {
+  if constexpr ((PAIR == kPair && I + 1 == P::passes) || (PAIR == kUnpair && I == 0)) {
     static_assert(NB == 2 * P::tpl, "two butterflies a thread");
     return it == 0 ? t : (t == 0 ? NB / 2 : NB - t);
   }
@@ -151,10 +180,10 @@ __device__ __forceinline__ int rx_butterfly(int t, int it) {
 // Pass I of a line on the thread's butterflies v[it][r] (inputs j + r N/R, j
 // = rx_butterfly), then the passes after it. The last pass hands its
 // outputs to dst(j, c, value, it, r), for position j + c, c the same in every
-// thread; a PAIR transform hands dst(j, c, value, mirror, it, r), mirror the
+// thread; a kPair transform hands dst(j, c, value, mirror, it, r), mirror the
 // value at position N - (j + c) (mod N). sync_last (uniform): dst writes the
 // LDS, so the last exchange ends with a barrier.
-template <class P, int I, bool INV, bool PAIR = false, class V, int IT, int R, class Dst>
+template <class P, int I, bool INV, int PAIR = kPlain, class V, int IT, int R, class Dst>
 __device__ __forceinline__ void rx_passes(double *buf, const cplx<double> *__restrict__ tw, int t, V (&v)[IT][R],
                                           bool sync_last, Dst dst) {
   constexpr int N = P::n, TPL = P::tpl, NS = P::ns(I), NB = N / R;
@@ -180,7 +209,7 @@ __device__ __forceinline__ void rx_passes(double *buf, const cplx<double> *__res
       if (NB % TPL == 0 || j < NB) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          if constexpr (PAIR) {
+          if constexpr (PAIR == kPair) {
             const V o = v[1 - it][R - 1 - r], s = it == 0 ? v[0][(R - r) % R] : v[1][R - 1 - r];
             dst(j, r * NS, v[it][r], mkc<double>(t ? o.x : s.x, t ? o.y : s.y), it, r);
           } else {
@@ -196,7 +225,7 @@ __device__ __forceinline__ void rx_passes(double *buf, const cplx<double> *__res
     for (int part = 0; part < 2; ++part) {
 #pragma unroll
       for (int it = 0; it < IT; ++it) {
-        const int j = t + it * TPL;
+        const int j = rx_butterfly<P, I, PAIR>(t, it);
         if (NB % TPL == 0 || j < NB) {
           // constant offsets from one slot of a butterfly where the padding
           // allows them

@@ -22,17 +22,6 @@
 
 namespace pf {
 
-constexpr int yr_tpl(int n) {
-  switch (n) {
-#define PF_CASE(N) \
-  case N:          \
-    return LinePlan<N>::tpl;
-    PF_FOR_LINE_PLANS(PF_CASE)
-#undef PF_CASE
-    default:
-      return 0;
-  }
-}
 template <typename T, int N, int LPW, bool INV, int YW, bool XR>
 __device__ __forceinline__ void yr_body(T *data, const cplx<double> *__restrict__ tw,
                                         const cplx<double> *__restrict__ ctw, int nx, int nib, size_t sp,
@@ -148,7 +137,7 @@ __device__ __forceinline__ void yr_body(T *data, const cplx<double> *__restrict_
           return (YW == 2 && (y & 1)) ? mkc<double>(-x.x, -x.y) : x;
         }
       });
-      rx_passes<Q, 0, false, true>(buf, tw, t, v, false, [&](int j, int c, const C &x, const C &m, int, int r) {
+      rx_passes<Q, 0, false, kPair>(buf, tw, t, v, false, [&](int j, int c, const C &x, const C &m, int, int r) {
         const int q = j + c;
         if constexpr (YW == 0) {
           constexpr int H = 4;  // positions q <= N/2, the half of the last pass's radix

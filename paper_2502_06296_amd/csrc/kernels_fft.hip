@@ -11,7 +11,7 @@
 // dominated by high wavenumbers, so its weakly damped low modes would lose
 // all their digits; rounding only at the stores keeps the per-mode error
 // relative to each stored value.
-#include "fft_kernels.hpp"
+#include "fft_x.hpp"
 #include "pf_internal.hpp"
 
 #include <algorithm>
@@ -289,29 +289,95 @@ template <int N, int TPL, int LPW>
 __global__ __launch_bounds__(TPL *LPW) void k_xfwd_grp(const GJobs g) {
   const GJob &J = g.j[blockIdx.y];
   if (blockIdx.x >= J.nblk) return;  // uniform per block
-  xfwd_body<float, N, TPL, LPW, true, 0>(static_cast<const double *>(J.in), static_cast<float *>(J.out),
-                                         J.tw, nullptr, J.sums, (long)J.ny * J.nz / 2, J.ny, J.sp,
-                                         blockIdx.x, J.nblk);
+  const double *f = static_cast<const double *>(J.in);
+  float *W = static_cast<float *>(J.out);
+  const long ncl = (long)J.ny * J.nz / 2;
+  if constexpr (x_fwd_in_regs<float>(N))
+    xr_fwd_body<float, N, LPW>(f, W, J.tw, J.sums, ncl, J.ny, J.sp, blockIdx.x);
+  else
+    xfwd_body<float, N, TPL, LPW, true, 0>(f, W, J.tw, nullptr, J.sums, ncl, J.ny, J.sp, blockIdx.x, J.nblk);
 }
 template <int N, int TPL, int LPW>
 __global__ __launch_bounds__(TPL *LPW) void k_resid_grp(const GJobs g) {
   const GJob &J = g.j[blockIdx.y];
   if (blockIdx.x >= J.nblk) return;
-  resid_spec_body<N, TPL, LPW, 0>(static_cast<const double *>(J.in), J.zm, static_cast<const float *>(J.in2),
-                                  static_cast<float *>(J.out), J.tw, nullptr, J.sums, J.sx, J.zal, J.zga,
-                                  J.zex, J.ny, J.nz, J.idy2, 1.0 / J.ny, 0, J.sp, blockIdx.x, J.nblk);
+  const double *f = static_cast<const double *>(J.in);
+  const float *W = static_cast<const float *>(J.in2);
+  float *R = static_cast<float *>(J.out);
+  if constexpr (resid_in_regs(N))
+    xr_resid_body<N, LPW>(f, J.zm, W, R, J.tw, J.sums, J.sx, J.zal, J.zga, J.zex, J.ny, J.nz, J.idy2, 1.0 / J.ny, 0,
+                          J.sp, blockIdx.x, J.nblk);
+  else
+    resid_spec_body<N, TPL, LPW, 0>(f, J.zm, W, R, J.tw, nullptr, J.sums, J.sx, J.zal, J.zga, J.zex, J.ny, J.nz,
+                                    J.idy2, 1.0 / J.ny, 0, J.sp, blockIdx.x, J.nblk);
 }
 template <int N, int TPL, int LPW>
 __global__ __launch_bounds__(TPL *LPW) void k_xinv_grp(const GJobs g) {
   const GJob &J = g.j[blockIdx.y];
   if (blockIdx.x >= J.nblk) return;
-  xinv_body<float, double, N, TPL, LPW, true, true, 0>(
-      static_cast<const float *>(J.in), static_cast<double *>(J.out), J.tw, nullptr, J.zm,
-      static_cast<const float *>(J.in2), J.scale, J.ny, (long)J.ny * J.nz / 2, J.sp, J.stat, blockIdx.x,
-      J.nblk);
+  const float *W = static_cast<const float *>(J.in), *D = static_cast<const float *>(J.in2);
+  double *p = static_cast<double *>(J.out);
+  const long ncl = (long)J.ny * J.nz / 2;
+  if constexpr (x_inv_in_regs<float>(N))
+    xr_inv_body<float, double, N, LPW, true>(W, p, J.tw, J.zm, D, J.scale, J.ny, ncl, J.sp, J.stat, blockIdx.x);
+  else
+    xinv_body<float, double, N, TPL, LPW, true, true, 0>(W, p, J.tw, nullptr, J.zm, D, J.scale, J.ny, ncl, J.sp,
+                                                         J.stat, blockIdx.x, J.nblk);
 }
 
 // ------------------------------------------------------------- launchers
+// the default launches of one length, periodic x: the register or the LDS
+// engine
+template <typename T, int N>
+static hipError_t xfwd_periodic(int ny, const double *in, T *out, size_t sp, const cplx<double> *tw, double *sums,
+                                long ncl, hipStream_t st) {
+  if constexpr (x_fwd_in_regs<T>(N)) {
+    constexpr int LPW = xr_lpw(N);
+    hipLaunchKernelGGL((k_xr_fwd<T, N, LPW>), dim3((unsigned)((ncl + LPW - 1) / LPW)),
+                       dim3(LinePlan<N>::tpl * LPW), 0, st, in, out, tw, sums, ncl, ny, sp);
+  } else {
+    constexpr int TPL = xfwd_tpl(N), LPW = x_lpw(N);
+    hipLaunchKernelGGL((k_xfwd<T, N, TPL, LPW, true, 0>), dim3((unsigned)((ncl + LPW - 1) / LPW)), dim3(TPL * LPW),
+                       0, st, in, out, tw, nullptr, sums, ncl, ny, sp);
+  }
+  return hipGetLastError();
+}
+template <int N>
+static hipError_t resid_periodic(int ny, int nz, const double *f, const double *fbar, const float *W, float *out,
+                                 size_t sp, const cplx<double> *tw, double *sums_p, const double *sx,
+                                 const double *zal, const double *zga, const double *zex, double idy2, int ywalls,
+                                 hipStream_t st) {
+  const double inv_ny = ywalls == 3 ? 0.5 / ny : 1.0 / ny;
+  if constexpr (resid_in_regs(N)) {
+    constexpr int LPW = xr_resid_lpw(N);
+    if (ny % (2 * LPW)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_xr_resid<N, LPW>), dim3((unsigned)((long)ny * nz / (2 * LPW))),
+                       dim3(LinePlan<N>::tpl * LPW), 0, st, f, fbar, W, out, tw, sums_p, sx, zal, zga, zex, ny, nz,
+                       idy2, inv_ny, ywalls, sp);
+  } else {
+    constexpr int TPL = resid_tpl(N), LPW = resid_lpw(N);
+    if (ny % (2 * LPW)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_resid_spec<N, TPL, LPW, 0>), dim3((unsigned)((long)ny * nz / (2 * LPW))), dim3(TPL * LPW),
+                       0, st, f, fbar, W, out, tw, nullptr, sums_p, sx, zal, zga, zex, ny, nz, idy2, inv_ny, ywalls,
+                       sp);
+  }
+  return hipGetLastError();
+}
+template <typename TS, typename TO, int N, bool SUM2>
+static hipError_t xinv_periodic(int ny, const TS *in, size_t sp, TO *out, const cplx<double> *tw, const double *zm,
+                                const TS *in2, double scale, long ncl, unsigned long long *stat, hipStream_t st) {
+  if constexpr (x_inv_in_regs<TS>(N)) {
+    constexpr int LPW = xr_lpw(N);
+    hipLaunchKernelGGL((k_xr_inv<TS, TO, N, LPW, SUM2>), dim3((unsigned)((ncl + LPW - 1) / LPW)),
+                       dim3(LinePlan<N>::tpl * LPW), 0, st, in, out, tw, zm, in2, scale, ny, ncl, sp, stat);
+  } else {
+    constexpr int TPL = x_tpl(N), LPW = x_lpw(N);
+    hipLaunchKernelGGL((k_xinv<TS, TO, N, TPL, LPW, true, SUM2, 0>), dim3((unsigned)((ncl + LPW - 1) / LPW)),
+                       dim3(TPL * LPW), 0, st, in, out, tw, nullptr, zm, in2, scale, ny, ncl, sp, stat);
+  }
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_xfwd(int nx, int ny, const double *in, T *out, size_t sp,
                        const cplx<double> *tw, double *sums, long lines, hipStream_t st, int xw,
@@ -352,8 +418,7 @@ hipError_t launch_xfwd(int nx, int ny, const double *in, T *out, size_t sp,
       hipLaunchKernelGGL((k_xfwd<T, N, TPL, LPW, true, 2>), g, dim3(TPL * LPW), 0, st, in, out,  \
                          tw, ctwx, sums, ncl, ny, sp);                                          \
     else if (sums)                                                                              \
-      hipLaunchKernelGGL((k_xfwd<T, N, TPL, LPW, true, 0>), g, dim3(TPL * LPW), 0, st, in, out,  \
-                         tw, ctwx, sums, ncl, ny, sp);                                          \
+      return xfwd_periodic<T, N>(ny, in, out, sp, tw, sums, ncl, st);                           \
     else                                                                                        \
       hipLaunchKernelGGL((k_xfwd<T, N, TPL, LPW, false, 0>), g, dim3(TPL * LPW), 0, st, in, out, \
                          tw, ctwx, sums, ncl, ny, sp);                                          \
@@ -401,15 +466,16 @@ hipError_t launch_resid_spec(int nx, int ny, int nz, const double *f, const doub
   switch (nx) {
 #define PF_CASE(N)                                                                               \
   case N: {                                                                                      \
+    if (xw == 0)                                                                                 \
+      return resid_periodic<N>(ny, nz, f, fbar, W, out, sp, tw, sums_p, sx, zal, zga, zex, idy2,  \
+                               ywalls, st);                                                      \
     constexpr int TPL = resid_tpl(N), LPW = resid_lpw(N);                                        \
     if (ny % (2 * LPW)) return hipErrorInvalidValue;                                             \
     const long nblk = (long)ny * nz / (2 * LPW);                                                 \
     if (xw == 1)                                                                                 \
       PF_RESID(N, 1);                                                                            \
-    else if (xw == 2)                                                                            \
-      PF_RESID(N, 2);                                                                            \
     else                                                                                         \
-      PF_RESID(N, 0);                                                                            \
+      PF_RESID(N, 2);                                                                            \
     return hipGetLastError();                                                                    \
   }
     PF_FOR_FFT_SIZES(PF_CASE)
@@ -469,9 +535,10 @@ hipError_t launch_xinv(int nx, int ny, const TS *in, size_t sp, TO *out, const c
     else if (xw == 2)                                                                           \
       PF_XINV(N, true, false, 2, nullptr);                                                         \
     else if (zm && in2)                                                                         \
-      PF_XINV(N, true, true, 0, stat);                                                             \
+      return xinv_periodic<TS, TO, N, true>(ny, in, sp, out, tw, zm, in2, scale, ncl, stat, st); \
     else if (zm)                                                                                \
-      PF_XINV(N, true, false, 0, nullptr);                                                         \
+      return xinv_periodic<TS, TO, N, false>(ny, in, sp, out, tw, zm, nullptr, scale, ncl,      \
+                                             nullptr, st);                                      \
     else                                                                                        \
       PF_XINV(N, false, false, 0, nullptr);                                                        \
     return hipGetLastError();                                                                   \
@@ -489,7 +556,8 @@ hipError_t launch_xfwd_grp(int nx, GJobs &g, hipStream_t st) {
   switch (nx) {
 #define PF_CASE(N)                                                                            \
   case N: {                                                                                   \
-    constexpr int TPL = xfwd_tpl(N), LPW = x_lpw(N);                                          \
+    constexpr bool R = x_fwd_in_regs<float>(N);                                               \
+    constexpr int TPL = R ? rx_tpl(N) : xfwd_tpl(N), LPW = R ? xr_lpw(N) : x_lpw(N);          \
     for (int k = 0; k < g.count; ++k) {                                                       \
       if (g.j[k].nx != N || g.j[k].ny % 2) return hipErrorInvalidValue;                       \
       g.j[k].nblk = (unsigned)(((long)g.j[k].ny * g.j[k].nz / 2 + LPW - 1) / LPW);            \
@@ -509,7 +577,8 @@ hipError_t launch_resid_grp(int nx, GJobs &g, hipStream_t st) {
   switch (nx) {
 #define PF_CASE(N)                                                                            \
   case N: {                                                                                   \
-    constexpr int TPL = resid_tpl(N), LPW = resid_lpw(N);                                     \
+    constexpr bool R = resid_in_regs(N);                                                      \
+    constexpr int TPL = R ? rx_tpl(N) : resid_tpl(N), LPW = R ? xr_resid_lpw(N) : resid_lpw(N); \
     for (int k = 0; k < g.count; ++k) {                                                       \
       if (g.j[k].nx != N || g.j[k].ny % (2 * LPW)) return hipErrorInvalidValue;               \
       g.j[k].nblk = (unsigned)((long)g.j[k].ny * g.j[k].nz / (2 * LPW));                      \
@@ -529,7 +598,8 @@ hipError_t launch_xinv_grp(int nx, GJobs &g, hipStream_t st) {
   switch (nx) {
 #define PF_CASE(N)                                                                            \
   case N: {                                                                                   \
-    constexpr int TPL = x_tpl(N), LPW = x_lpw(N);                                             \
+    constexpr bool R = x_inv_in_regs<float>(N);                                               \
+    constexpr int TPL = R ? rx_tpl(N) : x_tpl(N), LPW = R ? xr_lpw(N) : x_lpw(N);             \
     for (int k = 0; k < g.count; ++k) {                                                       \
       if (g.j[k].nx != N || g.j[k].ny % 2 || !g.j[k].zm) return hipErrorInvalidValue;         \
       g.j[k].nblk = (unsigned)(((long)g.j[k].ny * g.j[k].nz / 2 + LPW - 1) / LPW);            \

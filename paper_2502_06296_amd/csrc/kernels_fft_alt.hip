@@ -3,6 +3,7 @@
 // per workgroup, radix order), for the lengths 256, 512, 1024 and 2048. The
 // kernels are the templates of fft_kernels.hpp; the default shapes are
 // instantiated in kernels_fft.hip only.
+#include "fft_x.hpp"
 #include "fft_y.hpp"
 #include "pf_internal.hpp"
 
@@ -15,7 +16,12 @@ template <typename T, int N, int S>
 hipError_t xfwd_one(int ny, const double *in, T *out, size_t sp, const cplx<double> *tw, double *sums,
                     long ncl, hipStream_t st) {
   constexpr TShape h = xfwd_shape(N, S);
-  if constexpr (h.ok) {
+  if constexpr (h.ok && x_fwd_in_regs<T>(N) && S != 3) {
+    constexpr int LPW = S == 1 ? xr_lpw(N) / 2 : 2 * xr_lpw(N);
+    hipLaunchKernelGGL((k_xr_fwd<T, N, LPW>), dim3((unsigned)((ncl + LPW - 1) / LPW)),
+                       dim3(LinePlan<N>::tpl * LPW), 0, st, in, out, tw, sums, ncl, ny, sp);
+    return hipGetLastError();
+  } else if constexpr (h.ok) {
     hipLaunchKernelGGL((k_xfwd<T, N, h.tpl, h.lpw, true, 0, h.ro>), dim3((unsigned)((ncl + h.lpw - 1) / h.lpw)),
                        dim3(h.tpl * h.lpw), 0, st, in, out, tw, nullptr, sums, ncl, ny, sp);
     return hipGetLastError();
@@ -30,7 +36,14 @@ hipError_t resid_one(int ny, int nz, const double *f, const double *fbar, const 
                      const double *zal, const double *zga, const double *zex, double idy2, int ywalls,
                      hipStream_t st) {
   constexpr TShape h = resid_shape(N, S);
-  if constexpr (h.ok) {
+  if constexpr (h.ok && resid_in_regs(N) && S != 3) {
+    constexpr int LPW = S == 1 ? xr_resid_lpw(N) / 2 : xr_resid_lpw(N);
+    if (ny % (2 * LPW)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_xr_resid<N, LPW>), dim3((unsigned)((long)ny * nz / (2 * LPW))),
+                       dim3(LinePlan<N>::tpl * LPW), 0, st, f, fbar, W, out, tw, sums_p, sx, zal, zga, zex, ny, nz,
+                       idy2, ywalls == 3 ? 0.5 / ny : 1.0 / ny, ywalls, sp);
+    return hipGetLastError();
+  } else if constexpr (h.ok) {
     if (ny % (2 * h.lpw)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_resid_spec<N, h.tpl, h.lpw, 0, h.ro>), dim3((unsigned)((long)ny * nz / (2 * h.lpw))),
                        dim3(h.tpl * h.lpw), 0, st, f, fbar, W, out, tw, nullptr, sums_p, sx, zal, zga, zex,
@@ -74,7 +87,17 @@ template <typename TS, typename TO, int N, int S>
 hipError_t xinv_one(int ny, const TS *in, size_t sp, TO *out, const cplx<double> *tw, const double *zm,
                     const TS *in2, double scale, long ncl, hipStream_t st, unsigned long long *stat) {
   constexpr TShape h = xinv_shape(N, S);
-  if constexpr (h.ok) {
+  if constexpr (h.ok && x_inv_in_regs<TS>(N) && S != 3) {
+    constexpr int LPW = S == 1 ? xr_lpw(N) / 2 : 2 * xr_lpw(N);
+    const dim3 g((unsigned)((ncl + LPW - 1) / LPW)), b(LinePlan<N>::tpl * LPW);
+    if (in2)
+      hipLaunchKernelGGL((k_xr_inv<TS, TO, N, LPW, true>), g, b, 0, st, in, out, tw, zm, in2, scale, ny, ncl, sp,
+                         stat);
+    else
+      hipLaunchKernelGGL((k_xr_inv<TS, TO, N, LPW, false>), g, b, 0, st, in, out, tw, zm, in2, scale, ny, ncl, sp,
+                         nullptr);
+    return hipGetLastError();
+  } else if constexpr (h.ok) {
     const dim3 g((unsigned)((ncl + h.lpw - 1) / h.lpw)), b(h.tpl * h.lpw);
     if (in2)
       hipLaunchKernelGGL((k_xinv<TS, TO, N, h.tpl, h.lpw, true, true, 0, h.ro>), g, b, 0, st, in, out, tw,

@@ -12,7 +12,7 @@ template <typename T, int N, bool INV>
 hipError_t y_persist_one(int nx, int nz, T *data, size_t sp, const cplx<double> *tw, hipStream_t st,
                          const PlaneMean &pm) {
   constexpr bool kRegs = y_in_regs<T>(N);
-  constexpr int TPL = kRegs ? yr_tpl(N) : y_tpl(N), LPW = kRegs ? yr_lpw<T>(N) : y_lpw<T>(N);
+  constexpr int TPL = kRegs ? rx_tpl(N) : y_tpl(N), LPW = kRegs ? yr_lpw<T>(N) : y_lpw<T>(N);
   if (nx % (2 * LPW)) return hipErrorInvalidValue;
   const int nib = nx / (2 * LPW);
   const long nblk = (long)nib * nz;

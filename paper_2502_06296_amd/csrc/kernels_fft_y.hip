@@ -109,7 +109,7 @@ __global__ __launch_bounds__(TPL *LPW) void k_y_grp(const GJobs g) {
 template <int N, bool INV>
 static hipError_t y_grp_launch(GJobs &g, hipStream_t st) {
   constexpr bool kRegs = y_in_regs<float>(N);
-  constexpr int TPL = kRegs ? yr_tpl(N) : y_tpl(N), LPW = kRegs ? yr_lpw<float>(N) : y_lpw<float>(N);
+  constexpr int TPL = kRegs ? rx_tpl(N) : y_tpl(N), LPW = kRegs ? yr_lpw<float>(N) : y_lpw<float>(N);
   for (int k = 0; k < g.count; ++k) {
     if (g.j[k].ny != N || g.j[k].nx % (2 * LPW)) return hipErrorInvalidValue;
     g.j[k].nblk = (unsigned)(g.j[k].nx / (2 * LPW) * g.j[k].nz);

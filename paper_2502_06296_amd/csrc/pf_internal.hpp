@@ -134,6 +134,26 @@ constexpr int yr_lpw(int n) {
   return v;
 }
 
+// The periodic x transforms and the residual on the register engine (fft_x.hpp,
+// which has the times of both engines): the lengths that are faster there, and
+// the line pairs per workgroup (about 256 threads; the residual's divide ny,
+// which is a multiple of 16).
+template <typename T>
+constexpr bool x_fwd_in_regs(int n) {
+  return n >= (sizeof(T) == 8 ? 1024 : 384);
+}
+template <typename T>
+constexpr bool x_inv_in_regs(int n) {
+  return sizeof(T) == 8 ? n > 2048 || n == 1536 : n >= 768 || n == 384;
+}
+constexpr bool resid_in_regs(int n) { return n >= 256 && n != 1536; }
+constexpr int xr_lpw(int n) {
+  int v = 1;
+  while (2 * v * (n / 16) <= 256) v *= 2;
+  return v;
+}
+constexpr int xr_resid_lpw(int n) { return xr_lpw(n) > 8 ? 8 : xr_lpw(n); }
+
 // Launch shapes of the periodic transforms the autotuner chooses from, per
 // family: 0 the default above; 1 half the threads per line (twice the
 // values per thread); 2 twice the threads per line (x transforms and the
@@ -144,7 +164,7 @@ constexpr int yr_lpw(int n) {
 // compiler's fusion of multiply-adds), shape 3 in a different order of
 // passes. Where the default y transform is the register engine's, shape 1 is
 // half its lines per workgroup, shape 2 twice them (up to 16) and shape 3 the
-// LDS engine's.
+// LDS engine's; the same for the x transforms and the residual.
 // Shape 4 (y transforms only, every length): the default threads and lines
 // in a persistent launch; on the LDS engine it prefetches each workgroup's
 // next block (k_y_persist).
