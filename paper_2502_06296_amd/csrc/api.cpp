@@ -328,9 +328,10 @@ pf_status pcr_recompute(pf_pcr_plan *pl, double s, hipStream_t st) {
   return PF_OK;
 }
 
-pf::HelmCoef helm_coef(const pf_pcr_plan *pl) {
+// the plan's tables, in float64 or float32
+pf::HelmCoef helm_coef(const pf_pcr_plan *pl, bool f64) {
   pf::HelmCoef c;
-  const size_t *o = pl->prec == PF_FP64 ? pl->o_d : pl->o_f;
+  const size_t *o = f64 ? pl->o_d : pl->o_f;
   c.fa = pl->ar.base + o[0];
   c.bg = pl->ar.base + o[1];
   c.ib = pl->ar.base + o[2];
@@ -1269,21 +1270,31 @@ pf_status pcr_set_stream(pf_pcr_plan *pl, void *stream) {
   return PF_OK;
 }
 
-// Validates a group of Helmholtz fields for one fused launch and fills its
-// job table and launch shape.
+// A validated group of Helmholtz fields.
 struct HelmGroup {
   pf::HelmJob jobs[pf::kMaxHelmJobs];
-  int count = 0, M = 0, cw = 1 << 30, prec = 0;
-  bool staged = true;
+  const pf_pcr_plan *plans[pf::kMaxHelmJobs];
+  int count = 0;
 };
+
+// The arithmetic of a plan's apply (launch_helm's precision). A refined plan
+// whose chunks are narrower than a wave (columns of more than 512 rows)
+// eliminates once in float64: both move the same float64 field, and the
+// float32 solve, its float64 residual and the second solve do not fit the
+// registers beside the 32 rows of a chunk (three fields at 1024x1024x1024:
+// 14.77 ms with half the rows parked in LDS, 11.34 in float64, and an error of
+// 1e-16 instead of 3e-15). Up to 512 rows the refined solves are as fast
+// (512x384x256 0.463 against 0.493 ms).
+static int helm_mode(const pf_pcr_plan *pl) {
+  if (pl->prec == PF_FP32_REFINE) return pl->cw < 64 && !pl->staged ? 0 : 2;
+  return pl->prec == PF_FP64 ? 0 : 1;
+}
 
 static pf_status pcr_group(int32_t count, pf_pcr_plan *const *plans, void *const *fields, const int32_t *nx,
                            const int32_t *ny, HelmGroup &G) {
   if (count < 1 || count > pf::kMaxHelmJobs) return fail(PF_ERR_ARG, "count must be 1..%d", pf::kMaxHelmJobs);
   if (!plans || !fields || !nx || !ny) return fail(PF_ERR_ARG, "NULL argument array");
   pf::HelmJob *jobs = G.jobs;
-  int M = 0, cw = 1 << 30;
-  bool staged = true;
   for (int t = 0; t < count; ++t) {
     const pf_pcr_plan *pl = plans[t];
     if (!pl || !fields[t]) return fail(PF_ERR_ARG, "plan or field %d is NULL", t);
@@ -1293,13 +1304,11 @@ static pf_status pcr_group(int32_t count, pf_pcr_plan *const *plans, void *const
     if (pl->prec != plans[0]->prec) return fail(PF_ERR_ARG, "batched plans must share precision");
     const size_t esz = pl->prec == PF_FP32 ? 4 : 8;
     if ((uintptr_t)fields[t] % esz) return fail(PF_ERR_ARG, "field %d misaligned", t);
-    M = M > pl->M ? M : pl->M;
-    cw = cw < pl->cw ? cw : pl->cw;
-    staged = staged && pl->staged;
     jobs[t].field = fields[t];
     jobs[t].nx = nx[t];
     jobs[t].ny = ny[t];
-    jobs[t].c = helm_coef(pl);
+    jobs[t].c = helm_coef(pl, helm_mode(pl) == 0);
+    G.plans[t] = pl;
   }
   for (int t = 0; t < count; ++t)
     for (int u = t + 1; u < count; ++u) {
@@ -1308,16 +1317,32 @@ static pf_status pcr_group(int32_t count, pf_pcr_plan *const *plans, void *const
       if (overlaps(fields[t], a, fields[u], b)) return fail(PF_ERR_ARG, "fields %d and %d overlap", t, u);
     }
   G.count = count;
-  G.M = M;
-  G.cw = cw;
-  G.staged = staged;
-  G.prec = plans[0]->prec == PF_FP64 ? 0 : (plans[0]->prec == PF_FP32 ? 1 : 2);
   return PF_OK;
 }
 
+// One launch for the fields that share a kernel: one for the whole group,
+// unless its chunks are of different kinds.
 static pf_status pcr_enqueue(pf_pcr_plan *p0, const HelmGroup &G, hipStream_t st) {
-  return run_stage(p0->tm, st, PF_STAGE_PCR_APPLY,
-                   [&]() { return pf::launch_helm(G.prec, G.M, G.cw, G.staged, G.count, G.jobs, st); });
+  return run_stage(p0->tm, st, PF_STAGE_PCR_APPLY, [&]() {
+    bool done[pf::kMaxHelmJobs] = {};
+    for (int first = 0; first < G.count; ++first) {
+      if (done[first]) continue;
+      const pf_pcr_plan *p = G.plans[first];
+      const int mode = helm_mode(p);
+      pf::HelmJob jobs[pf::kMaxHelmJobs];
+      int n = 0, cw = p->cw;
+      for (int t = first; t < G.count; ++t) {
+        const pf_pcr_plan *q = G.plans[t];
+        if (done[t] || q->staged != p->staged || helm_mode(q) != mode) continue;
+        jobs[n++] = G.jobs[t];
+        cw = cw < q->cw ? cw : q->cw;
+        done[t] = true;
+      }
+      const hipError_t e = pf::launch_helm(mode, p->M, cw, p->staged, n, jobs, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  });
 }
 
 pf_status pcr_apply_batched(int32_t count, pf_pcr_plan *const *plans, void *const *fields, const int32_t *nx,
