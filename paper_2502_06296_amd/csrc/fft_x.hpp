@@ -13,6 +13,9 @@
 //            float64  3200 x 3456 x 28  1.20 -> 0.98                2048 x 1024 x 128  0.757 -> 0.764
 //   inverse  float32  1024 x 512 x 512  0.806 -> 0.739 (5.8 TB/s)   3456 x 3072 x 30  1.50 -> 1.07
 //            float64  3200 x 3456 x 28  1.05 -> 0.93                1024 x 512 x 512  0.742 -> 0.798
+//   divergence float64  1024 x 512 x 256  1.152 -> 0.816 (5.3 TB/s)   3200 x 3456 x 28  5.68 -> 2.32
+//            refined  512 x 512 x 512  1.326 -> 0.928 (5.2 TB/s)   3456 x 1024 x 30  1.76 -> 0.82
+//            (192 x 96 x 100 0.025 -> 0.028, refined 0.025 -> 0.031: the LDS engine stays there)
 //   residual          512 x 512 x 512   0.580 -> 0.513              3456 x 3072 x 30  2.22 -> 1.59
 //                     1024 x 512 x 512  1.049 -> 1.042              1536 x 512 x 256  0.846 -> 0.876
 #pragma once
@@ -43,11 +46,39 @@ __device__ __forceinline__ void xr_forward(double *buf, const cplx<double> *__re
                                 });
 }
 
+// The two spectra of pair c from src, packed as in k_xfwd, into out; c past
+// the last pair (ok false) stores nothing.
+template <typename T, int N, class Src>
+__device__ __forceinline__ void xr_pair(double *buf, T *__restrict__ out, const cplx<double> *__restrict__ tw,
+                                        double *__restrict__ sums, long c, int ny, size_t sp, int t, bool ok,
+                                        Src src) {
+  using C = cplx<double>;
+  T *oa = out + (size_t)(2 * c / ny) * sp + (size_t)(2 * c % ny) * N;
+  T *ob = oa + N;
+  xr_forward<N>(buf, tw, t, src, [&](int q, const C &z, const C &m, int r) {
+    if (!ok) return;
+    if (r < 4 && q != 0) {
+      C A, B;
+      split_pair<double>(z, m, A, B);
+      st2<T>(oa + 2 * q, A.x, A.y);
+      st2<T>(ob + 2 * q, B.x, B.y);
+    } else if (q == 0) {
+      oa[0] = (T)z.x;
+      ob[0] = (T)z.y;
+      // the float64 zero mode of each line is its sum
+      sums[2 * c] = z.x;
+      sums[2 * c + 1] = z.y;
+    } else if (2 * q == N) {
+      oa[1] = (T)z.x;
+      ob[1] = (T)z.y;
+    }
+  });
+}
+
 template <typename T, int N, int LPW>
 __device__ __forceinline__ void xr_fwd_body(const double *__restrict__ in, T *__restrict__ out,
                                             const cplx<double> *__restrict__ tw, double *__restrict__ sums, long ncl,
                                             int ny, size_t sp, unsigned bx_) {
-  using C = cplx<double>;
   constexpr int TPL = LinePlan<N>::tpl;
   __shared__ double lds[LPW * xr_stride(N)];
   const int l = threadIdx.x / TPL, t = threadIdx.x % TPL;
@@ -56,28 +87,8 @@ __device__ __forceinline__ void xr_fwd_body(const double *__restrict__ in, T *__
   // a workgroup's lines past the last pair transform the last pair again
   const long cc = ok ? c : ncl - 1;
   const double *a = in + (size_t)(2 * cc) * N, *b = a + N;
-  T *oa = out + (size_t)(2 * cc / ny) * sp + (size_t)(2 * cc % ny) * N;
-  T *ob = oa + N;
-  xr_forward<N>(
-      lds + l * xr_stride(N), tw, t, [&](int i) { return mkc<double>(a[i], b[i]); },
-      [&](int q, const C &z, const C &m, int r) {
-        if (!ok) return;
-        if (r < 4 && q != 0) {
-          C A, B;
-          split_pair<double>(z, m, A, B);
-          st2<T>(oa + 2 * q, A.x, A.y);
-          st2<T>(ob + 2 * q, B.x, B.y);
-        } else if (q == 0) {
-          oa[0] = (T)z.x;
-          ob[0] = (T)z.y;
-          // the float64 zero mode of each line is its sum
-          sums[2 * c] = z.x;
-          sums[2 * c + 1] = z.y;
-        } else if (2 * q == N) {
-          oa[1] = (T)z.x;
-          ob[1] = (T)z.y;
-        }
-      });
+  xr_pair<T, N>(lds + l * xr_stride(N), out, tw, sums, cc, ny, sp, t, ok,
+                [&](int i) { return mkc<double>(a[i], b[i]); });
 }
 template <typename T, int N, int LPW>
 __global__ __launch_bounds__(LinePlan<N>::tpl *LPW) void k_xr_fwd(const double *__restrict__ in,
@@ -86,6 +97,46 @@ __global__ __launch_bounds__(LinePlan<N>::tpl *LPW) void k_xr_fwd(const double *
                                                                    double *__restrict__ sums, long ncl, int ny,
                                                                    size_t sp) {
   xr_fwd_body<T, N, LPW>(in, out, tw, sums, ncl, ny, sp, blockIdx.x);
+}
+
+// The forward of a projection's right-hand side, formed as the positions are
+// read (as k_xfwd_div, periodic x). It has eleven reads per position pair:
+// half the LDS of k_xfwd_div gives twice the waves, and all of a position's
+// reads are unconditional (past a wall the line itself is read and its value
+// dropped), so they are in flight together; the pass then runs at the copy
+// rate of its 32 (refined 36) bytes a point, but for the longest lines.
+template <typename T, int N, int LPW, bool STASH>
+__global__ __launch_bounds__(LinePlan<N>::tpl *LPW) void k_xr_div(DivArgs d, T *__restrict__ out,
+                                                                   const cplx<double> *__restrict__ tw,
+                                                                   double *__restrict__ sums, long ncl, int ny,
+                                                                   int nz, size_t sp) {
+  constexpr int TPL = LinePlan<N>::tpl;
+  __shared__ double lds[LPW * xr_stride(N)];
+  const int l = threadIdx.x / TPL, t = threadIdx.x % TPL;
+  const long c = (long)blockIdx.x * LPW + l;
+  const bool ok = c < ncl;
+  const long cc = ok ? c : ncl - 1;
+  const int k = (int)(2 * cc / ny), j = (int)(2 * cc % ny);
+  const size_t o = (size_t)(2 * cc) * N;
+  const bool top = k < nz - 1, bot = k > 0, south = !(d.ywalls && j == 0), north = !(d.ywalls && j + 2 == ny);
+  const double *u = d.u + o, *v = d.v + o;
+  const double *vm = d.v + ((size_t)k * ny + (j == 0 ? ny - 1 : j - 1)) * N;
+  const double *wt = top ? d.w + o : u, *wb = bot ? d.w + (o - (size_t)ny * N) : u;
+  const double rz = d.rdzf[k];
+  double *f = STASH ? d.stash + o : nullptr;
+  xr_pair<T, N>(lds + l * xr_stride(N), out, tw, sums, cc, ny, sp, t, ok, [&](int i) {
+    const int im = i == 0 ? N - 1 : i - 1;
+    const double v0 = v[i], vs = vm[i], vn = v[N + i], ta = wt[i], tb = wt[N + i], ba = wb[i], bb = wb[N + i];
+    double fa = (u[i] - u[im]) * d.idx + (v0 - (south ? vs : 0.0)) * d.idy;
+    double fb = (u[N + i] - u[N + im]) * d.idx + ((north ? vn : 0.0) - v0) * d.idy;
+    fa = (fa + (top ? ta : 0.0) * rz - (bot ? ba : 0.0) * rz) * d.igdt;
+    fb = (fb + (top ? tb : 0.0) * rz - (bot ? bb : 0.0) * rz) * d.igdt;
+    if (STASH && ok) {
+      f[i] = fa;
+      f[N + i] = fb;
+    }
+    return mkc<double>(fa, fb);
+  });
 }
 
 // ------------------------------------------------------------- x inverse

@@ -228,6 +228,28 @@ hipError_t launch_status_final(unsigned long long *stat, double tol, bool refine
   return hipGetLastError();
 }
 
+// Periodic x: the lengths that are faster on the register engine there.
+template <typename T, int N>
+hipError_t xfwd_div_periodic(const DivArgs &d, T *out, const cplx<double> *tw, double *sums, long ncl, int ny, int nz,
+                             size_t sp, hipStream_t st) {
+  if constexpr (x_div_in_regs(N)) {
+    constexpr int LPW = xr_lpw(N);
+    const dim3 g((unsigned)((ncl + LPW - 1) / LPW)), b(LinePlan<N>::tpl * LPW);
+    if (d.stash)
+      hipLaunchKernelGGL((k_xr_div<T, N, LPW, true>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
+    else
+      hipLaunchKernelGGL((k_xr_div<T, N, LPW, false>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
+  } else {
+    constexpr int TPL = xfwd_tpl(N), LPW = x_lpw(N);
+    const dim3 g((unsigned)((ncl + LPW - 1) / LPW)), b(TPL * LPW);
+    if (d.stash)
+      hipLaunchKernelGGL((k_xfwd_div<T, N, TPL, LPW, true>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
+    else
+      hipLaunchKernelGGL((k_xfwd_div<T, N, TPL, LPW, false>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
+  }
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_xfwd_div(int nx, int ny, int nz, const DivArgs &d, T *out, size_t sp,
                            const cplx<double> *tw, double *sums, hipStream_t st) {
@@ -236,20 +258,15 @@ hipError_t launch_xfwd_div(int nx, int ny, int nz, const DivArgs &d, T *out, siz
   switch (nx) {
 #define PF_CASE(N)                                                                               \
   case N: {                                                                                      \
+    if (!d.xwalls) return xfwd_div_periodic<T, N>(d, out, tw, sums, ncl, ny, nz, sp, st);        \
     constexpr int TPL = xfwd_tpl(N), LPW = x_lpw(N);                                             \
     dim3 g((unsigned)((ncl + LPW - 1) / LPW));                                                   \
-    if (d.xwalls && d.stash)                                                                     \
+    if (d.stash)                                                                                 \
       hipLaunchKernelGGL((k_xfwd_div<T, N, TPL, LPW, true, 1>), g, dim3(TPL * LPW), 0, st, d,    \
                          out, tw, sums, ncl, ny, nz, sp);                                        \
-    else if (d.xwalls)                                                                           \
+    else                                                                                         \
       hipLaunchKernelGGL((k_xfwd_div<T, N, TPL, LPW, false, 1>), g, dim3(TPL * LPW), 0, st, d,   \
                          out, tw, sums, ncl, ny, nz, sp);                                        \
-    else if (d.stash)                                                                            \
-      hipLaunchKernelGGL((k_xfwd_div<T, N, TPL, LPW, true>), g, dim3(TPL * LPW), 0, st, d, out,  \
-                         tw, sums, ncl, ny, nz, sp);                                             \
-    else                                                                                         \
-      hipLaunchKernelGGL((k_xfwd_div<T, N, TPL, LPW, false>), g, dim3(TPL * LPW), 0, st, d, out, \
-                         tw, sums, ncl, ny, nz, sp);                                             \
     return hipGetLastError();                                                                    \
   }
     PF_FOR_FFT_SIZES(PF_CASE)

@@ -146,6 +146,7 @@ template <typename T>
 constexpr bool x_inv_in_regs(int n) {
   return sizeof(T) == 8 ? n > 2048 || n == 1536 : n >= 768 || n == 384;
 }
+constexpr bool x_div_in_regs(int n) { return n >= 256; }
 constexpr bool resid_in_regs(int n) { return n >= 256 && n != 1536; }
 constexpr int xr_lpw(int n) {
   int v = 1;
