@@ -631,7 +631,8 @@ def headline(args):
         "scaling": "weak", "vs_baseline": None, "dtype": "f32+f64-residual", "data": "synthetic",
         "config": {"workload": f"projection step: 3 z-Helmholtz (u,v centres; w faces; one batched "
                                f"launch) + pressure Poisson, {NX}x{NY}x{NZ} channel, tanh {BETA}, "
-                               "float32 with one float64-residual correction and a float64 zero mode",
+                               "float32 with one float64-residual correction and a float64 zero mode "
+                               "(Helmholtz columns above 512 rows: one float64 elimination)",
                    "nx": NX, "ny": NY, "nz": NZ, "beta": BETA, "s": S_HELM,
                    "precision": "fp32_refine", "parallelism": "1 GPU",
                    "inputs": "seeded device draws: f uniform[-1,1] mean removed, u v w N(0,1)"},
