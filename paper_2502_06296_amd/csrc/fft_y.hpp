@@ -14,13 +14,26 @@
 //   float32  3456 points, 3200 x 3456 x 28    1.54 / 1.50 -> 1.10 / 1.00  (2.3)
 //   float64  3456 points, 3200 x 3456 x 28    1.83 / 1.81 -> 1.40 / 1.22  (3.8)
 //   float64  2048 points, 1024 x 2048 x 128   1.17 / 1.16 -> 0.94 / 0.94  (4.6)
-// Walls (PairPlan forward, both rows of a mirror pair read twice inverse):
-// the refined Poisson solve at 1024 x 512 x 512 with y walls 6.36 -> 5.81.
+// Walls, the inverse with both rows of a mirror pair read twice and with every
+// row read once (UnpairPlan; yr_unpair):
+//   float32   512 points, 1024 x 512 x 512    0.568 -> 0.487
+//   float64  1024 points, 1024 x 1024 x 256   0.919 -> 0.828, sine 1.164 -> 0.826
+//   float64  3072 points, 3456 x 3072 x 30    1.55 -> 1.45
 #pragma once
 #include "fft_kernels.hpp"
 #include "fft_regs.hpp"
 
 namespace pf {
+
+// The wall inverses that read every row once (ms at the head of this file).
+// They start with radix 8 instead of 16, which takes a pass more at 192, 256
+// and from 3072 points: 192, 384, 2048 and 3200 points lose by it (float32
+// 0.189 -> 0.212, 0.497 -> 0.546, 0.757 -> 0.851, 0.800 -> 0.844 ms), and 3456
+// float32 points (1.21 -> 1.24; float64 1.60 -> 1.54).
+template <typename T>
+constexpr bool yr_unpair(int n) {
+  return n != 192 && n != 384 && n != 2048 && n != 3200 && (n != 3456 || sizeof(T) == 8);
+}
 
 template <typename T, int N, int LPW, bool INV, int YW, bool XR>
 __device__ __forceinline__ void yr_body(T *data, const cplx<double> *__restrict__ tw,
@@ -124,7 +137,8 @@ __device__ __forceinline__ void yr_body(T *data, const cplx<double> *__restrict_
     } else {
     // walls in y (or in x, XR): every line's spectrum is folded with its
     // mirror image. Forward, a thread of the PAIR transform holds both
-    // positions; inverse, it reads both rows (the second time from cache).
+    // positions; inverse, a thread of the UNPAIR transform does, or it reads
+    // both rows (the second time from cache; packed spectra always).
     if constexpr (!INV) {
       using Q = PairPlan<N>;
       typename RxFirst<Q>::Regs v;
@@ -156,34 +170,66 @@ __device__ __forceinline__ void yr_body(T *data, const cplx<double> *__restrict_
               w.x * x.y + w.y * x.x + w.x * m.y - w.y * m.x);
         }
       });
-    } else {
+    } else if constexpr (YW == 0) {
       typename RxFirst<L>::Regs v;
       rx_load<L>(v, t, [&](int j, int c) {
-        const int n = j + c;
-        if constexpr (YW == 0) {
-          // position n of the joined packed real spectra
-          const int q = n <= N / 2 ? n : N - n;
-          if (q == 0 || 2 * q == N) return at(q == 0 ? 0 : 1, 0);
-          const C r0 = at(2 * q, 0), r1 = at(2 * q + 1, 0);
-          const double s = 2 * n < N ? 1.0 : -1.0;
-          return mkc<double>(r0.x - s * r1.y, r0.y + s * r1.x);
-        } else {
-          // conj(c) (X_n - i X_{N-n}) / 2, X_N = 0
+        // position n of the joined packed real spectra
+        const int n = j + c, q = n <= N / 2 ? n : N - n;
+        if (q == 0 || 2 * q == N) return at(q == 0 ? 0 : 1, 0);
+        const C r0 = at(2 * q, 0), r1 = at(2 * q + 1, 0);
+        const double s = 2 * n < N ? 1.0 : -1.0;
+        return mkc<double>(r0.x - s * r1.y, r0.y + s * r1.x);
+      });
+      rx_passes<L, 0, true>(buf, tw, t, v, false, [&](int j, int c, const C &x, int, int) { put(j, c, x.x, x.y); });
+    } else {
+      // the wall's rows: position n takes conj(c_n) (X_n - i X_{N-n}) / 2, X_N = 0
+      auto dst = [&](int j, int c, const C &x, int, int) {
+        const int n = j + c, y = n < N / 2 ? 2 * n : 2 * N - 1 - 2 * n;
+        const double sg = (YW == 2 && (y & 1)) ? -1.0 : 1.0;
+        put(y, 0, sg * x.x, sg * x.y);
+      };
+      if constexpr (!yr_unpair<T>(N)) {
+        typename RxFirst<L>::Regs v;
+        rx_load<L>(v, t, [&](int j, int c) {
+          const int n = j + c;
           const C x = at(YW == 2 ? N - 1 - n : n, 0), w = ctw[n];
           const C z = n == 0 ? mkc<double>(0.0, 0.0) : at(YW == 2 ? n - 1 : N - n, 0);
           const double ur = 0.5 * (x.x + z.y), ui = 0.5 * (x.y - z.x);
           return mkc<double>(w.x * ur + w.y * ui, w.x * ui - w.y * ur);
+        });
+        rx_passes<L, 0, true>(buf, tw, t, v, false, dst);
+      } else {
+        // every row read once: the mirror image of butterfly j, position r, is
+        // N/8 - j, position 7 - r; that of butterfly 0 is its own position
+        // 8 - r, that of N/16 (the other one of thread 0) its own 7 - r
+        using Q = UnpairPlan<N>;
+        constexpr int NB = N / 8;
+        cplx<T> X[2][8];
+        typename RxFirst<Q>::Regs v;
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+          const int j = rx_butterfly<Q, 0, kUnpair>(t, it);
+#pragma unroll
+          for (int r = 0; r < 8; ++r) {
+            const C x = YW == 2 ? at(NB - 1 - j, (7 - r) * NB) : at(j, r * NB);
+            X[it][r] = mkc<T>((T)x.x, (T)x.y);
+          }
         }
-      });
-      rx_passes<L, 0, true>(buf, tw, t, v, false, [&](int j, int c, const C &x, int, int) {
-        if constexpr (YW == 0) {
-          put(j, c, x.x, x.y);
-        } else {
-          const int n = j + c, y = n < N / 2 ? 2 * n : 2 * N - 1 - 2 * n;
-          const double sg = (YW == 2 && (y & 1)) ? -1.0 : 1.0;
-          put(y, 0, sg * x.x, sg * x.y);
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+          const int j = rx_butterfly<Q, 0, kUnpair>(t, it);
+#pragma unroll
+          for (int r = 0; r < 8; ++r) {
+            const cplx<T> x = X[it][r], m = X[1 - it][7 - r], o = X[it][(it ? 7 - r : 8 - r) % 8];
+            const bool none = it == 0 && r == 0 && t == 0;
+            const T zx = none ? T(0) : t ? m.x : o.x, zy = none ? T(0) : t ? m.y : o.y;
+            const C w = ctw[j + r * NB];
+            const double ur = 0.5 * ((double)x.x + zy), ui = 0.5 * ((double)x.y - zx);
+            v[it][r] = mkc<double>(w.x * ur + w.y * ui, w.x * ui - w.y * ur);
+          }
         }
-      });
+        rx_passes<Q, 0, true, kUnpair>(buf, tw, t, v, false, dst);
+      }
     }
     }
   }
