@@ -414,7 +414,7 @@ static pf_status channel_plan(pf_poisson_plan **out, const pf_grid *g, int32_t p
                                       "and precision", g->nx, 2 * lpw);
   }
   const int nzu = bc == PF_BC_DIRICHLET_FACE ? g->nz - 1 : g->nz;  // planes of the field
-  int zc = pf::zsolve_default_variant(g->nx, g->ny, nzu, precision == PF_FP64);
+  int zc = pf::zsolve_default_variant(g->nx, g->ny, nzu, precision == PF_FP64, g->xbc != PF_X_PERIODIC);
   if (const char *ev = std::getenv("PF_ZSOLVE_VARIANT")) {
     const int v = std::atoi(ev);
     if (pf::zsolve_variant_fits(v, g->nx, nzu, precision == PF_FP64 ? 8 : 4)) zc = v;

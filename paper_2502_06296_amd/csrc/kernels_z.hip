@@ -1037,7 +1037,7 @@ bool zsolve_variant_fits(int v, int nx, int nz, int esize) {
          zsolve_lds(z, P, esize) <= (z.maxt > 512 || z.tile ? 160 * 1024 : 65536);
 }
 
-int zsolve_default_variant(int nx, int ny, int nz, bool fp64) {
+int zsolve_default_variant(int nx, int ny, int nz, bool fp64, bool xr) {
   // Float32 storage: the persistent shapes, 32-column tiles while a column has
   // at most 16 chunks (3456 x 3072 x 30 0.53 against 0.80 ms with 16 columns;
   // 256 x 256 x 192 0.039 against 0.033).
@@ -1047,22 +1047,37 @@ int zsolve_default_variant(int nx, int ny, int nz, bool fp64) {
   // double-buffered reduced rows; 28 11.30, 20 11.52, the tiled 31 12.8, 4
   // 22.2). Planes of up to 131072 columns do not fill the chip with those
   // shapes: 18 (8 rows, 8 columns: 256x256x384 0.078 against 0.106 ms,
-  // 512x256x193 0.071 against 0.078; at 512x512x128 0.123 against 0.110), and
-  // up to 65536 columns of 16 chunks the persistent 41 (64x64x64 8.1 against
-  // 10.5 us). Other short columns (few chunks) would leave the first shapes
-  // with tiny workgroups, so the first fitting shape with at least 128 threads
-  // wins, widened by the 64- and 128-column shapes; the unpaired 4 and 3 are
-  // fall-backs where the LDS or thread budget excludes the paired shapes.
+  // 512x256x193 0.071 against 0.078), as long as the field stays in the 256 MB
+  // last-level cache, which is where its 64-byte row segments cost nothing
+  // (2^25 points and more lose: 384x256x300 0.084 against 0.124 ms, but
+  // 384x256x384 0.197 against 0.165, 256x128x1024 0.154 against 0.138). Up to
+  // 65536 columns of 16 chunks the persistent 41 (64x64x64 8.1 against 10.5 us,
+  // 256x256x128 31 against 35). Other short columns (few chunks) would leave
+  // the first shapes with tiny workgroups, so the first fitting shape with at
+  // least 128 threads wins, widened by the 64- and 128-column shapes; the
+  // unpaired 4 and 3 are fall-backs where the LDS or thread budget excludes the
+  // paired shapes.
+  // x walls (xr): a persistent workgroup reads every tile once for each of its
+  // two passes, which the direct shapes do not. Float64 takes 41 up to 8192
+  // columns only (64x64x64 9.2 against 11.5 us; 128x128x64 19.0 against 16.3,
+  // 256x256x16 24 against 13). Float32 storage takes the 128-column 24 for
+  // planes of 65536 columns and more of at most 16 rows (512x512x16 20 against
+  // 24 us; 128x128x16 11 against 8, 512x512x24 28 against 26), and the tiled 39
+  // for 161-256 rows of a cached field of 131072 columns and more (512x512x256
+  // 0.241 against 0.280 ms, 512x256x192 0.094 against 0.102; 512x512x160 0.172
+  // against 0.171, 1024x512x192 beyond the cache 0.475 against 0.439).
   static const int f64[] = {40, 21, 10, 19, 38, 26, 25, 24, 23, 20, 8, 4, 3}, f32[] = {42, 41};
-  const long cols = (long)nx * ny;
+  const long cols = (long)nx * ny, cached = (1l << 28) / (fp64 ? 8 : 4);
   auto fits = [&](int v) { return zsolve_variant_fits(v, nx, nz, fp64 ? 8 : 4); };
   if (!fp64) {
+    if (xr && cols >= 65536 && nz <= 16 && fits(24)) return 24;
+    if (xr && cols >= 131072 && nz > 160 && nz <= 256 && cols * nz <= cached && fits(39)) return 39;
     for (int v : f32)
       if (fits(v)) return v;
     return -1;
   }
-  if (cols <= 65536 && fits(41)) return 41;
-  if (cols <= 131072 && nz > 64 && fits(18)) return 18;
+  if (cols <= (xr ? 8192 : 65536) && fits(41)) return 41;
+  if (cols <= 131072 && nz > 64 && cols * nz < cached && fits(18)) return 18;
   auto threads = [&](int v) {
     const ZVariant &z = kZVariants[v];
     const int P = (nz + z.M - 1) / z.M;

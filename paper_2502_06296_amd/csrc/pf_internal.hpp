@@ -339,7 +339,8 @@ hipError_t launch_zsolve(int nx, int ny, int nz, TS *data, size_t sp, const doub
                          int variant, hipStream_t st, bool xr = false, const ZeroJob &zj = ZeroJob{});
 int zsolve_variant_count();
 bool zsolve_variant_fits(int variant, int nx, int nz, int esize);  // esize: bytes per stored value
-int zsolve_default_variant(int nx, int ny, int nz, bool fp64);
+// xr: x walls, so that every column pair is solved in two passes
+int zsolve_default_variant(int nx, int ny, int nz, bool fp64, bool xr);
 
 // ----------------------------------------------------- grouped launches
 // One launch runs one stage of several independent problems that share the
