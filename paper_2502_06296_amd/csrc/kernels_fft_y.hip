@@ -10,29 +10,36 @@
 namespace pf {
 
 namespace {
+template <typename T>
+int y_lines_of(int n, bool inv, int yw, bool xr, long slots, long planes) {
+  if (!y_in_regs<T>(n) || y_lds_mode<T>(n, inv, yw, xr)) return 0;
+  const int lpw = yr_lpw<T>(n);
+  const long wgs = slots * planes / (2 * lpw);
+  if (wgs <= y_lds_wgs<T>(n, inv, yw, xr)) return 0;
+  // 48 slots (an x-face field of the shortest lines) need the narrow ones
+  return wgs <= y_narrow_wgs<T>(n) || slots % (2 * lpw) ? yr_narrow<T>(n) : lpw;
+}
+template <typename T, int N, int LPW, bool INV, int YW, bool XR>
+hipError_t yr_launch(int nx, int nz, T *data, size_t sp, const cplx<double> *tw, const cplx<double> *ctw,
+                     const PlaneMean &pm, hipStream_t st) {
+  if (nx % (2 * LPW)) return hipErrorInvalidValue;
+  const int nib = nx / (2 * LPW);
+  hipLaunchKernelGGL((k_yr<T, N, LPW, INV, YW, XR>), dim3((unsigned)((long)nib * nz)),
+                     dim3(LinePlan<N>::tpl * LPW), 0, st, data, tw, ctw, nx, nib, sp, pm);
+  return hipGetLastError();
+}
 // Kernels of one length: the register engine (k_yr) or the LDS engine (k_yfwd,
 // k_yinv).
 template <typename T, int N, bool INV, int YW, bool XR>
 hipError_t y_launch(int nx, int nz, T *data, size_t sp, const cplx<double> *tw, const cplx<double> *ctw,
                     const PlaneMean &pm, hipStream_t st) {
-  if constexpr (y_in_regs<T>(N)) {
-    constexpr int LPW = yr_lpw<T>(N), TPL = LinePlan<N>::tpl;
-    if (nx % (2 * LPW) == 0) {
-      const int nib = nx / (2 * LPW);
-      hipLaunchKernelGGL((k_yr<T, N, LPW, INV, YW, XR>), dim3((unsigned)((long)nib * nz)), dim3(TPL * LPW), 0, st,
-                         data, tw, ctw, nx, nib, sp, pm);
-      return hipGetLastError();
-    }
-    // half the columns (48 slots, an x-face field of the shortest lines)
-    if constexpr (LPW > 8) {
-      if (nx % LPW) return hipErrorInvalidValue;
-      const int nib = nx / LPW;
-      hipLaunchKernelGGL((k_yr<T, N, LPW / 2, INV, YW, XR>), dim3((unsigned)((long)nib * nz)), dim3(TPL * LPW / 2),
-                         0, st, data, tw, ctw, nx, nib, sp, pm);
-      return hipGetLastError();
-    }
-    return hipErrorInvalidValue;
-  } else {
+  if constexpr (y_in_regs<T>(N) && !y_lds_mode<T>(N, INV, YW, XR)) {
+    constexpr int LPW = yr_lpw<T>(N), LN = yr_narrow<T>(N);
+    const int lines = y_lines_of<T>(N, INV, YW, XR, nx, nz);
+    if (lines == LPW) return yr_launch<T, N, LPW, INV, YW, XR>(nx, nz, data, sp, tw, ctw, pm, st);
+    if (lines) return yr_launch<T, N, LN, INV, YW, XR>(nx, nz, data, sp, tw, ctw, pm, st);
+  }
+  if constexpr (!y_in_regs<T>(N) || y_lds_mode<T>(N, INV, YW, XR) || y_lds_wgs<T>(N, INV, YW, XR) > 0) {
     constexpr int TPL = y_tpl(N), LPW = y_lpw<T>(N);
     if (nx % (2 * LPW)) return hipErrorInvalidValue;
     const int nib = nx / (2 * LPW);
@@ -43,6 +50,7 @@ hipError_t y_launch(int nx, int nz, T *data, size_t sp, const cplx<double> *tw, 
       hipLaunchKernelGGL((k_yfwd<T, N, TPL, LPW, YW, XR>), g, b, 0, st, data, tw, ctw, nx, nib, sp, pm);
     return hipGetLastError();
   }
+  return hipErrorInvalidValue;
 }
 
 template <typename T, bool INV>
@@ -64,6 +72,10 @@ hipError_t y_any(int nx, int ny, int nz, T *data, size_t sp, const cplx<double> 
   }
 }
 }  // namespace
+
+int y_lines(bool fp64, int n, bool inv, int yw, bool xr, int nx, int nz) {
+  return fp64 ? y_lines_of<double>(n, inv, yw, xr, nx, nz) : y_lines_of<float>(n, inv, yw, xr, nx, nz);
+}
 
 template <typename T>
 hipError_t launch_yfwd(int nx, int ny, int nz, T *data, size_t sp, const cplx<double> *tw,
@@ -106,16 +118,28 @@ __global__ __launch_bounds__(TPL *LPW) void k_y_grp(const GJobs g) {
     yfwd_body<float, N, TPL, LPW, 0, false>(W, J.tw, nullptr, J.nx, nib, J.sp, grp_mean(J), blockIdx.x, J.nblk);
 }
 
-template <int N, bool INV>
-static hipError_t y_grp_launch(GJobs &g, hipStream_t st) {
-  constexpr bool kRegs = y_in_regs<float>(N);
-  constexpr int TPL = kRegs ? rx_tpl(N) : y_tpl(N), LPW = kRegs ? yr_lpw<float>(N) : y_lpw<float>(N);
+template <int N, int TPL, int LPW, bool INV>
+static hipError_t y_grp_run(GJobs &g, hipStream_t st) {
   for (int k = 0; k < g.count; ++k) {
     if (g.j[k].ny != N || g.j[k].nx % (2 * LPW)) return hipErrorInvalidValue;
     g.j[k].nblk = (unsigned)(g.j[k].nx / (2 * LPW) * g.j[k].nz);
   }
   hipLaunchKernelGGL((k_y_grp<N, TPL, LPW, INV>), grp_grid(g), dim3(TPL * LPW), 0, st, g);
   return hipGetLastError();
+}
+// the lines of a group's workgroups by all its jobs
+template <int N, bool INV>
+static hipError_t y_grp_launch(GJobs &g, hipStream_t st) {
+  if constexpr (y_in_regs<float>(N)) {
+    static_assert(!y_lds_mode<float>(N, INV, 0, false) && y_lds_wgs<float>(N, INV, 0, false) == 0, "periodic float32");
+    constexpr int LPW = yr_lpw<float>(N), LN = yr_narrow<float>(N);
+    long slots = 0;
+    for (int k = 0; k < g.count; ++k) slots += (long)g.j[k].nx * g.j[k].nz;
+    if (y_lines_of<float>(N, INV, 0, false, slots, 1) == LPW) return y_grp_run<N, rx_tpl(N), LPW, INV>(g, st);
+    return y_grp_run<N, rx_tpl(N), LN, INV>(g, st);
+  } else {
+    return y_grp_run<N, y_tpl(N), y_lpw<float>(N), INV>(g, st);
+  }
 }
 template <bool INV>
 static hipError_t launch_y_grp(int ny, GJobs &g, hipStream_t st) {

@@ -114,11 +114,11 @@ constexpr int y_lpw(int n) {
 
 // The y transforms of the register engine (fft_regs.hpp, fft_y.hpp): the
 // lengths it takes (the LDS engine keeps the shorter ones, where it is as
-// fast: 512 float64 points 0.75 against 0.78 ms at 1024 x 512 x 512; from 192
-// float32 and 768 float64 points on the register engine is ahead, 1024
+// fast: 512 float64 points 0.75 against 0.78 ms at 1024 x 512 x 512; 1024
 // float32 points 0.90 against 1.37 ms at 1024 x 1024 x 512), and its lines per
 // workgroup, 2 LPW contiguous values of every row: 128 bytes where
-// about 100 KB of LDS hold the lines (8 bytes a point). Fewer lines in two
+// about 100 KB of LDS hold the lines (8 bytes a point), 64 for 384 float32
+// points (0.46 against 0.33 ms at 1024 x 384 x 512). Fewer lines in two
 // workgroups of a compute unit are slower: 3072 float32 points 0.97 ms with
 // 4 lines in one workgroup, 1.43 ms with 2 lines in two.
 template <typename T>
@@ -127,12 +127,64 @@ constexpr bool y_in_regs(int n) {
 }
 template <typename T>
 constexpr int yr_lpw(int n) {
-  const int want = sizeof(T) == 8 ? 8 : 16;
+  const int want = sizeof(T) == 8 || n == 384 ? 8 : 16;
   const int fit = 13900 / n;
   int v = 2;
   while (v * 2 <= want && v * 2 <= fit) v *= 2;
   return v;
 }
+// Narrow workgroups, for launches that leave compute units idle: half the
+// lines (a quarter at 768 float32 points) up to y_narrow_wgs workgroups of all
+// of them. 128 would be half the compute units: 1024 float32 points on 2^20
+// values 13 us with all 8 lines, 11 with 4; 3072 points on 2^21 20 and 17, on
+// 2^22 (171 workgroups) 20 and 27. The workgroups of 512 and 768 float32 and of 768
+// float64 points leave room for one or two in a compute unit only, and lose
+// to narrow ones until several rounds hide it: 512 points on 2^24 values 32
+// against 28 us, on 2^28 0.41 against 0.42 ms; 768 float32 points on 2^24 43
+// and 31, on 2^26 0.15 and 0.16 forward, 0.13 and 0.10 inverse; 768 float64 points on
+// 2^24 60 and 47, on 2^26 0.22 and 0.20. 192 and 256 points fill the chip either way.
+template <typename T>
+constexpr int yr_narrow(int n) {
+  const int v = yr_lpw<T>(n) / (sizeof(T) == 4 && n == 768 ? 4 : 2);
+  return v < 2 ? 2 : v;
+}
+template <typename T>
+constexpr long y_narrow_wgs(int n) {
+  if (sizeof(T) == 4 && n < 384) return 0;
+  if (n == 512) return 2048;
+  if (n == 768) return sizeof(T) == 4 ? 4096 : 8192;
+  return 128;
+}
+// The transforms that the LDS engine runs faster at any size: faces of 128,
+// 512 (the inverse) and 1024 rows (256 x 1024 slots and rows on 2^26 values:
+// float32 forward 0.288 against 0.305 ms, inverse 0.223 / 0.254; 512 rows'
+// inverse 0.194 / 0.234, float64 0.275 / 0.297), and the inverse behind x
+// walls, which reads every row twice, of the shorter lengths (512 float32
+// points on 2^24 values 35 / 37 us, on 2^20 10 / 14; 1024 float64 points on
+// 2^26 0.195 / 0.213 ms, 2048 on 2^24 56 / 67 us).
+template <typename T>
+constexpr bool y_lds_mode(int n, bool inv, int yw, bool xr) {
+  if (yw == 3) return n == 2048 || (inv && n == 1024) || n == 256;
+  if (xr && inv) return n <= 1024 || (sizeof(T) == 8 && n == 2048);
+  return false;
+}
+// The LDS engine up to this many workgroups (of the register engine), where it
+// is the faster one on small fields: periodic float64 lines while the field
+// stays in the last-level cache (2^22 values of 1024 points 17 against 19 us;
+// 2048 points on 2^24 54 / 67, but on 2^26 0.32 / 0.26 ms), faces (256 rows
+// of float32 on 2^21 values 13 / 15 us, on 2^23 31 / 29), the long inverses behind x walls (3072
+// points on 2^21 values 16 / 18), the walls' forward of 192 and 256 points
+// (2^22 values 12 / 13.5, but on 2^26 121 / 110).
+template <typename T>
+constexpr long y_lds_wgs(int n, bool inv, int yw, bool xr) {
+  if (yw == 3) return n == 768 ? 192 : n <= 1024 ? 352 : 0;
+  if (xr && inv) return 128;
+  if (sizeof(T) == 4) return n <= 256 && !inv && (yw || xr) ? 512 : 0;
+  return yw == 0 && !xr && n <= 2048 ? (n == 768 ? 192 : 1024) : 0;
+}
+// What these rules choose for nx slots and nz planes of n points: lines per
+// workgroup of the register engine, 0 for the LDS engine.
+int y_lines(bool fp64, int n, bool inv, int yw, bool xr, int nx, int nz);
 
 // The periodic x transforms and the residual on the register engine (fft_x.hpp,
 // which has the times of both engines): the lengths that are faster there, and

@@ -36,3 +36,38 @@ Z_DEFAULTS = [
 def test_default_z_solve_is_the_faster_one(grid, fp64, xwalls, shape):
     rule = _rule("_ZN2pf22zsolve_default_variantEiiibb", C.c_int, C.c_int, C.c_int, C.c_bool, C.c_bool)
     assert rule(*grid, fp64, xwalls) == shape
+
+
+# (float64, points, inverse, walls, behind x walls, slots, planes), the lines of
+# a workgroup of the register engine, 0 for the LDS engine
+Y_LINES = [
+    ((True, 512, False, 0, False, 512, 512), 0), ((False, 128, False, 0, False, 512, 512), 0),
+    # full workgroups, and narrow ones where those leave compute units idle
+    ((False, 256, False, 0, False, 64, 64), 16), ((False, 1024, False, 0, False, 64, 256), 8),
+    ((False, 1024, False, 0, False, 64, 16), 4), ((False, 3072, True, 0, False, 64, 11), 2),
+    ((False, 3072, True, 0, False, 64, 22), 4), ((True, 3456, False, 1, False, 64, 10), 2),
+    ((False, 384, False, 0, False, 1024, 512), 8), ((False, 512, True, 0, False, 512, 64), 8),
+    ((False, 512, True, 0, False, 1024, 512), 16), ((False, 768, False, 0, False, 512, 40), 4),
+    ((False, 768, False, 0, False, 1024, 256), 16), ((True, 768, False, 1, False, 256, 340), 4),
+    ((True, 768, True, 0, False, 1024, 512), 8),
+    # 48 slots
+    ((False, 256, False, 1, False, 48, 1000), 8), ((False, 512, False, 1, False, 48, 512), 8),
+    # cached float64 lines; walls of the same size
+    ((True, 1024, False, 0, False, 512, 32), 0), ((True, 2048, True, 0, False, 512, 16), 0),
+    ((True, 1024, False, 0, False, 1024, 512), 8), ((True, 2048, True, 0, False, 1024, 128), 4),
+    ((True, 1024, False, 1, False, 512, 32), 8), ((True, 2048, True, 1, False, 512, 16), 4),
+    # faces, and the inverse behind x walls
+    ((False, 2048, False, 3, False, 256, 128), 0), ((True, 2048, True, 3, False, 256, 128), 0),
+    ((False, 1024, True, 3, False, 256, 128), 0), ((False, 1024, False, 3, False, 256, 128), 8),
+    ((False, 1536, True, 3, False, 256, 128), 8), ((False, 512, True, 0, True, 256, 128), 0),
+    ((False, 512, False, 0, True, 1024, 256), 16), ((False, 3072, True, 0, True, 64, 11), 0),
+    ((False, 512, False, 3, False, 64, 128), 0), ((False, 512, False, 3, False, 512, 64), 8), ((False, 256, False, 1, False, 512, 16), 0),
+    ((False, 256, True, 1, False, 512, 16), 16), ((False, 256, False, 1, False, 1024, 256), 16), ((True, 1024, True, 0, True, 256, 256), 0),
+    ((False, 1536, True, 0, True, 256, 128), 8), ((True, 1536, True, 0, True, 256, 128), 8),
+]
+
+
+@pytest.mark.parametrize("case,lines", Y_LINES)
+def test_y_transform_lines_are_the_faster_ones(case, lines):
+    rule = _rule("_ZN2pf7y_linesEbibibii", C.c_bool, C.c_int, C.c_bool, C.c_int, C.c_bool, C.c_int, C.c_int)
+    assert rule(*case) == lines
