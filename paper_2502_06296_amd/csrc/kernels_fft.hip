@@ -345,19 +345,33 @@ __global__ __launch_bounds__(TPL *LPW) void k_xinv_grp(const GJobs g) {
 // ------------------------------------------------------------- launchers
 // the default launches of one length, periodic x: the register or the LDS
 // engine
+int x_lines(int pass, bool fp64, int n, long pairs) {
+  if (pass == kXResidual) return resid_in_regs(n) ? xr_resid_lpw(n) : 0;
+  const bool regs = pass == kXForward ? (fp64 ? x_fwd_in_regs<double>(n) : x_fwd_in_regs<float>(n))
+                                      : (fp64 ? x_inv_in_regs<double>(n) : x_inv_in_regs<float>(n));
+  if (!regs) return 0;
+  return pairs <= 128l * xr_lpw(n) ? xr_half(n) : xr_lpw(n);
+}
+template <typename T, int N, int LPW>
+static hipError_t xr_fwd_launch(int ny, const double *in, T *out, size_t sp, const cplx<double> *tw, double *sums,
+                                long ncl, hipStream_t st) {
+  hipLaunchKernelGGL((k_xr_fwd<T, N, LPW>), dim3((unsigned)((ncl + LPW - 1) / LPW)), dim3(LinePlan<N>::tpl * LPW), 0,
+                     st, in, out, tw, sums, ncl, ny, sp);
+  return hipGetLastError();
+}
 template <typename T, int N>
 static hipError_t xfwd_periodic(int ny, const double *in, T *out, size_t sp, const cplx<double> *tw, double *sums,
                                 long ncl, hipStream_t st) {
   if constexpr (x_fwd_in_regs<T>(N)) {
-    constexpr int LPW = xr_lpw(N);
-    hipLaunchKernelGGL((k_xr_fwd<T, N, LPW>), dim3((unsigned)((ncl + LPW - 1) / LPW)),
-                       dim3(LinePlan<N>::tpl * LPW), 0, st, in, out, tw, sums, ncl, ny, sp);
+    if (x_lines(kXForward, sizeof(T) == 8, N, ncl) == xr_lpw(N))
+      return xr_fwd_launch<T, N, xr_lpw(N)>(ny, in, out, sp, tw, sums, ncl, st);
+    return xr_fwd_launch<T, N, xr_half(N)>(ny, in, out, sp, tw, sums, ncl, st);
   } else {
     constexpr int TPL = xfwd_tpl(N), LPW = x_lpw(N);
     hipLaunchKernelGGL((k_xfwd<T, N, TPL, LPW, true, 0>), dim3((unsigned)((ncl + LPW - 1) / LPW)), dim3(TPL * LPW),
                        0, st, in, out, tw, nullptr, sums, ncl, ny, sp);
+    return hipGetLastError();
   }
-  return hipGetLastError();
 }
 template <int N>
 static hipError_t resid_periodic(int ny, int nz, const double *f, const double *fbar, const float *W, float *out,
@@ -380,19 +394,26 @@ static hipError_t resid_periodic(int ny, int nz, const double *f, const double *
   }
   return hipGetLastError();
 }
+template <typename TS, typename TO, int N, int LPW, bool SUM2>
+static hipError_t xr_inv_launch(int ny, const TS *in, size_t sp, TO *out, const cplx<double> *tw, const double *zm,
+                                const TS *in2, double scale, long ncl, unsigned long long *stat, hipStream_t st) {
+  hipLaunchKernelGGL((k_xr_inv<TS, TO, N, LPW, SUM2>), dim3((unsigned)((ncl + LPW - 1) / LPW)),
+                     dim3(LinePlan<N>::tpl * LPW), 0, st, in, out, tw, zm, in2, scale, ny, ncl, sp, stat);
+  return hipGetLastError();
+}
 template <typename TS, typename TO, int N, bool SUM2>
 static hipError_t xinv_periodic(int ny, const TS *in, size_t sp, TO *out, const cplx<double> *tw, const double *zm,
                                 const TS *in2, double scale, long ncl, unsigned long long *stat, hipStream_t st) {
   if constexpr (x_inv_in_regs<TS>(N)) {
-    constexpr int LPW = xr_lpw(N);
-    hipLaunchKernelGGL((k_xr_inv<TS, TO, N, LPW, SUM2>), dim3((unsigned)((ncl + LPW - 1) / LPW)),
-                       dim3(LinePlan<N>::tpl * LPW), 0, st, in, out, tw, zm, in2, scale, ny, ncl, sp, stat);
+    if (x_lines(kXInverse, sizeof(TS) == 8, N, ncl) == xr_lpw(N))
+      return xr_inv_launch<TS, TO, N, xr_lpw(N), SUM2>(ny, in, sp, out, tw, zm, in2, scale, ncl, stat, st);
+    return xr_inv_launch<TS, TO, N, xr_half(N), SUM2>(ny, in, sp, out, tw, zm, in2, scale, ncl, stat, st);
   } else {
     constexpr int TPL = x_tpl(N), LPW = x_lpw(N);
     hipLaunchKernelGGL((k_xinv<TS, TO, N, TPL, LPW, true, SUM2, 0>), dim3((unsigned)((ncl + LPW - 1) / LPW)),
                        dim3(TPL * LPW), 0, st, in, out, tw, nullptr, zm, in2, scale, ny, ncl, sp, stat);
+    return hipGetLastError();
   }
-  return hipGetLastError();
 }
 
 template <typename T>
@@ -568,20 +589,33 @@ hipError_t launch_xinv(int nx, int ny, const TS *in, size_t sp, TO *out, const c
   }
 }
 
+// line pairs of a group's jobs
+static long grp_pairs(const GJobs &g) {
+  long n = 0;
+  for (int k = 0; k < g.count; ++k) n += (long)g.j[k].ny * g.j[k].nz / 2;
+  return n;
+}
+template <int N, int TPL, int LPW>
+static hipError_t xfwd_grp_run(GJobs &g, hipStream_t st) {
+  for (int k = 0; k < g.count; ++k) {
+    if (g.j[k].nx != N || g.j[k].ny % 2) return hipErrorInvalidValue;
+    g.j[k].nblk = (unsigned)(((long)g.j[k].ny * g.j[k].nz / 2 + LPW - 1) / LPW);
+  }
+  hipLaunchKernelGGL((k_xfwd_grp<N, TPL, LPW>), grp_grid(g), dim3(TPL * LPW), 0, st, g);
+  return hipGetLastError();
+}
 hipError_t launch_xfwd_grp(int nx, GJobs &g, hipStream_t st) {
   if (!grp_ok(g)) return hipErrorInvalidValue;
   switch (nx) {
 #define PF_CASE(N)                                                                            \
-  case N: {                                                                                   \
-    constexpr bool R = x_fwd_in_regs<float>(N);                                               \
-    constexpr int TPL = R ? rx_tpl(N) : xfwd_tpl(N), LPW = R ? xr_lpw(N) : x_lpw(N);          \
-    for (int k = 0; k < g.count; ++k) {                                                       \
-      if (g.j[k].nx != N || g.j[k].ny % 2) return hipErrorInvalidValue;                       \
-      g.j[k].nblk = (unsigned)(((long)g.j[k].ny * g.j[k].nz / 2 + LPW - 1) / LPW);            \
-    }                                                                                         \
-    hipLaunchKernelGGL((k_xfwd_grp<N, TPL, LPW>), grp_grid(g), dim3(TPL * LPW), 0, st, g);    \
-    return hipGetLastError();                                                                 \
-  }
+  case N:                                                                                     \
+    if constexpr (x_fwd_in_regs<float>(N)) {                                                  \
+      if (x_lines(kXForward, false, N, grp_pairs(g)) == xr_lpw(N))                            \
+        return xfwd_grp_run<N, rx_tpl(N), xr_lpw(N)>(g, st);                                  \
+      return xfwd_grp_run<N, rx_tpl(N), xr_half(N)>(g, st);                                   \
+    } else {                                                                                  \
+      return xfwd_grp_run<N, xfwd_tpl(N), x_lpw(N)>(g, st);                                   \
+    }
     PF_FOR_FFT_SIZES(PF_CASE)
 #undef PF_CASE
     default:
@@ -610,20 +644,27 @@ hipError_t launch_resid_grp(int nx, GJobs &g, hipStream_t st) {
   }
 }
 
+template <int N, int TPL, int LPW>
+static hipError_t xinv_grp_run(GJobs &g, hipStream_t st) {
+  for (int k = 0; k < g.count; ++k) {
+    if (g.j[k].nx != N || g.j[k].ny % 2 || !g.j[k].zm) return hipErrorInvalidValue;
+    g.j[k].nblk = (unsigned)(((long)g.j[k].ny * g.j[k].nz / 2 + LPW - 1) / LPW);
+  }
+  hipLaunchKernelGGL((k_xinv_grp<N, TPL, LPW>), grp_grid(g), dim3(TPL * LPW), 0, st, g);
+  return hipGetLastError();
+}
 hipError_t launch_xinv_grp(int nx, GJobs &g, hipStream_t st) {
   if (!grp_ok(g)) return hipErrorInvalidValue;
   switch (nx) {
 #define PF_CASE(N)                                                                            \
-  case N: {                                                                                   \
-    constexpr bool R = x_inv_in_regs<float>(N);                                               \
-    constexpr int TPL = R ? rx_tpl(N) : x_tpl(N), LPW = R ? xr_lpw(N) : x_lpw(N);             \
-    for (int k = 0; k < g.count; ++k) {                                                       \
-      if (g.j[k].nx != N || g.j[k].ny % 2 || !g.j[k].zm) return hipErrorInvalidValue;         \
-      g.j[k].nblk = (unsigned)(((long)g.j[k].ny * g.j[k].nz / 2 + LPW - 1) / LPW);            \
-    }                                                                                         \
-    hipLaunchKernelGGL((k_xinv_grp<N, TPL, LPW>), grp_grid(g), dim3(TPL * LPW), 0, st, g);    \
-    return hipGetLastError();                                                                 \
-  }
+  case N:                                                                                     \
+    if constexpr (x_inv_in_regs<float>(N)) {                                                  \
+      if (x_lines(kXInverse, false, N, grp_pairs(g)) == xr_lpw(N))                            \
+        return xinv_grp_run<N, rx_tpl(N), xr_lpw(N)>(g, st);                                  \
+      return xinv_grp_run<N, rx_tpl(N), xr_half(N)>(g, st);                                   \
+    } else {                                                                                  \
+      return xinv_grp_run<N, x_tpl(N), x_lpw(N)>(g, st);                                      \
+    }
     PF_FOR_FFT_SIZES(PF_CASE)
 #undef PF_CASE
     default:

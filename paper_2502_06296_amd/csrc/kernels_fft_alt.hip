@@ -37,7 +37,7 @@ hipError_t resid_one(int ny, int nz, const double *f, const double *fbar, const 
                      hipStream_t st) {
   constexpr TShape h = resid_shape(N, S);
   if constexpr (h.ok && resid_in_regs(N) && S != 3) {
-    constexpr int LPW = S == 1 ? xr_resid_lpw(N) / 2 : xr_resid_lpw(N);
+    constexpr int LPW = S == 1 ? xr_resid_lpw(N) / 2 : 2 * xr_resid_lpw(N);
     if (ny % (2 * LPW)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_xr_resid<N, LPW>), dim3((unsigned)((long)ny * nz / (2 * LPW))),
                        dim3(LinePlan<N>::tpl * LPW), 0, st, f, fbar, W, out, tw, sums_p, sx, zal, zga, zex, ny, nz,

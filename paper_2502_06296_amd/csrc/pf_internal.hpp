@@ -187,25 +187,40 @@ constexpr long y_lds_wgs(int n, bool inv, int yw, bool xr) {
 int y_lines(bool fp64, int n, bool inv, int yw, bool xr, int nx, int nz);
 
 // The periodic x transforms and the residual on the register engine (fft_x.hpp,
-// which has the times of both engines): the lengths that are faster there, and
-// the line pairs per workgroup (about 256 threads; the residual's divide ny,
-// which is a multiple of 16).
+// which has the times of both engines): the lengths that are faster there.
+// The forward leaves 512 float32 and 1024, 2048 and 3072 float64 points to the
+// LDS engine (512 x 512 x 512 0.298 against 0.312 ms, 1024 x 512 x 512 float64
+// 0.757 / 0.771, 2048 x 1024 x 256 1.50 / 1.53, 3072 points on 2^26 values
+// 0.202 / 0.214), the inverse 512 float32 points (0.383 / 0.403 ms) and the
+// float64 powers of two (1024 x 512 x 512 0.769 / 0.824), the residual 384, 768,
+// 1024 and 1536 points (384 points on 2^23 values 32 / 35 us, 768 on 2^24
+// 55 / 61, 1024 x 512 x 512 1.05 / 1.08 ms, 1536 x 512 x 256 0.845 / 0.920).
 template <typename T>
 constexpr bool x_fwd_in_regs(int n) {
-  return n >= (sizeof(T) == 8 ? 1024 : 384);
+  return sizeof(T) == 8 ? n == 1536 || n > 3072 : n >= 384 && n != 512;
 }
 template <typename T>
 constexpr bool x_inv_in_regs(int n) {
   return sizeof(T) == 8 ? n > 2048 || n == 1536 : n >= 768 || n == 384;
 }
 constexpr bool x_div_in_regs(int n) { return n >= 256; }
-constexpr bool resid_in_regs(int n) { return n >= 256 && n != 1536; }
+constexpr bool resid_in_regs(int n) { return n == 256 || n == 512 || n >= 2048; }
+// Line pairs per workgroup: about 256 threads; half of that where all the
+// workgroups would leave half the compute units without one (1024 float32
+// points on 2^20 values: forward 10.0 against 8.6 us, inverse 9.6 / 8.5). The residual's
+// divide ny, which is a multiple of 16; 4 are faster than 8 for 256 and 512
+// points (2^26 values 0.305 / 0.281 and 0.262 / 0.256 ms).
 constexpr int xr_lpw(int n) {
   int v = 1;
   while (2 * v * (n / 16) <= 256) v *= 2;
   return v;
 }
-constexpr int xr_resid_lpw(int n) { return xr_lpw(n) > 8 ? 8 : xr_lpw(n); }
+constexpr int xr_half(int n) { return xr_lpw(n) < 2 ? 1 : xr_lpw(n) / 2; }
+constexpr int xr_resid_lpw(int n) { return xr_lpw(n) > 4 ? 4 : xr_lpw(n); }
+// What these rules choose for `pairs` line pairs of n points: line pairs per
+// workgroup of the register engine, 0 for the LDS engine.
+enum : int { kXForward = 0, kXInverse = 1, kXResidual = 2 };
+int x_lines(int pass, bool fp64, int n, long pairs);
 
 // Launch shapes of the periodic transforms the autotuner chooses from, per
 // family: 0 the default above; 1 half the threads per line (twice the

@@ -71,3 +71,24 @@ Y_LINES = [
 def test_y_transform_lines_are_the_faster_ones(case, lines):
     rule = _rule("_ZN2pf7y_linesEbibibii", C.c_bool, C.c_int, C.c_bool, C.c_int, C.c_bool, C.c_int, C.c_int)
     assert rule(*case) == lines
+
+
+# (pass, float64, points, line pairs), the line pairs of a workgroup of the
+# register engine, 0 for the LDS engine
+FWD, INV, RESID = 0, 1, 2
+X_LINES = [
+    ((FWD, False, 256, 1 << 16), 0), ((FWD, False, 512, 1 << 18), 0), ((FWD, False, 768, 1 << 16), 4),
+    ((FWD, True, 1024, 1 << 17), 0), ((FWD, True, 2048, 1 << 15), 0), ((FWD, True, 3072, 1 << 15), 0),
+    ((FWD, True, 1536, 1 << 15), 2), ((FWD, True, 3456, 1 << 15), 1),
+    ((FWD, False, 1024, 513), 4), ((FWD, False, 1024, 512), 2), ((FWD, False, 3200, 100), 1),
+    ((INV, False, 512, 1 << 18), 0), ((INV, False, 384, 1 << 16), 8), ((INV, False, 2048, 200), 1),
+    ((INV, True, 2048, 1 << 15), 0), ((INV, True, 3456, 1 << 15), 1),
+    ((RESID, False, 384, 1 << 14), 0), ((RESID, False, 512, 1 << 17), 4), ((RESID, False, 768, 1 << 14), 0),
+    ((RESID, False, 1024, 1 << 17), 0), ((RESID, False, 1536, 1 << 16), 0), ((RESID, False, 2048, 1 << 15), 2),
+]
+
+
+@pytest.mark.parametrize("case,lines", X_LINES)
+def test_x_transform_lines_are_the_faster_ones(case, lines):
+    rule = _rule("_ZN2pf7x_linesEibil", C.c_int, C.c_bool, C.c_int, C.c_long)
+    assert rule(*case) == lines
