@@ -907,20 +907,27 @@ __global__ __launch_bounds__(PS *TP, z4_waves<TS>()) void k_zsolve4(TS *data, in
   zsolve4_body<TS, M, TP, PS>(data, nx, ny, nz, P, zal, zga, zex, sx, sy, sp, xr, bx, G);
 }
 // Several problems of one chunk count (see GJobs), float32 and periodic x;
-// J.nblk is the job's share of the resident workgroups.
+// J.nblk is the job's share of the resident workgroups. The grid is the zero
+// modes' workgroups, then every job's share, without gaps: a block that only
+// exits would still wait for a compute unit of its own, and with it the
+// blocks behind it (one workgroup a compute unit at 1024 rows).
 template <int M, int TP, int PS>
 __global__ __launch_bounds__(PS *TP, z4_waves<float>()) void k_zsolve4_grp(const GJobs g) {
-  const GJob &J = g.j[blockIdx.y];
-  unsigned bx = blockIdx.x;
-  if (J.in2) {  // the job's first workgroup takes its zero mode
-    if (bx == 0)
+  unsigned b = blockIdx.x;
+  for (int k = 0; k < g.count; ++k) {  // uniform
+    const GJob &J = g.j[k];
+    if (!J.in2) continue;
+    if (b == 0)
       return zero_solve(ZeroJob{J.zm, J.aux, const_cast<double *>(static_cast<const double *>(J.in2))}, J.zga,
                         J.nz);
-    --bx;
+    --b;
   }
-  if (bx >= J.nblk) return;  // uniform per block
+  int k = 0;
+  while (k < g.count && b >= g.j[k].nblk) b -= g.j[k++].nblk;
+  if (k == g.count) return;  // uniform
+  const GJob &J = g.j[k];
   zsolve4_body<float, M, TP, PS>(static_cast<float *>(J.out), J.nx, J.ny, J.nz, J.P, J.zal, J.zga, J.zex, J.sx,
-                                 J.sy, J.sp, 0, bx, J.nblk);
+                                 J.sy, J.sp, 0, b, J.nblk);
 }
 
 // one z-solve shape for several problems with the same chunk count (see
@@ -1113,22 +1120,44 @@ static hipError_t launch_z4(int nx, int ny, int nz, TS *data, size_t sp, const d
                      st, data, nx, ny, nz, P, zal, zga, zex, sx, sy, sp, (int)xr, zj);
   return hipGetLastError();
 }
+// Each job's share of the resident workgroups, by its tiles: rounded down (one
+// at least), then one more for whichever job has the most tiles a workgroup. They sum to
+// `resident` at most: a workgroup beyond it would start its tiles when a whole
+// round of others has ended theirs.
+void z_group_shares(long resident, int count, const long *tiles, unsigned *share) {
+  long total = 0, used = 0;
+  for (int k = 0; k < count; ++k) total += tiles[k];
+  for (int k = 0; k < count; ++k) {
+    share[k] = (unsigned)(total <= resident ? tiles[k] : std::max(1l, resident * tiles[k] / total));
+    used += share[k];
+  }
+  for (; used < resident; ++used) {
+    int most = -1;
+    for (int k = 0; k < count; ++k)
+      if (share[k] < tiles[k] && (most < 0 || tiles[k] * share[most] > tiles[most] * share[k])) most = k;
+    if (most < 0) break;
+    ++share[most];
+  }
+  // one workgroup for each of many tiny jobs comes out of the largest share
+  for (; used > resident; --used) {
+    unsigned *const big = std::max_element(share, share + count);
+    if (*big < 2) break;
+    --*big;
+  }
+}
 template <int M, int TP, int PS>
 static hipError_t launch_z4_grp(GJobs &g, int P, hipStream_t st) {
   const long res = z4_resident<float, M, TP, PS>(P);
   if (P > PS || res < 1) return hipErrorInvalidValue;
-  // each job's share of the resident workgroups, by its tiles
-  long total = 0;
-  for (int k = 0; k < g.count; ++k) total += (long)(g.j[k].nx / (2 * TP) + 1) * g.j[k].ny;
-  unsigned mb = 1;
+  long tiles[kMaxGroupJobs];
+  unsigned share[kMaxGroupJobs], nb = 0;
+  for (int k = 0; k < g.count; ++k) tiles[k] = (long)(g.j[k].nx / (2 * TP) + 1) * g.j[k].ny;
+  z_group_shares(res, g.count, tiles, share);
   for (int k = 0; k < g.count; ++k) {
-    GJob &J = g.j[k];
-    const long n = (long)(J.nx / (2 * TP) + 1) * J.ny;
-    J.nblk = (unsigned)std::min<long>(n, std::max<long>(1, (res * n + total - 1) / total));
-    mb = std::max(mb, J.nblk + (J.in2 ? 1 : 0));
+    g.j[k].nblk = share[k];
+    nb += share[k] + (g.j[k].in2 ? 1 : 0);
   }
-  hipLaunchKernelGGL((k_zsolve4_grp<M, TP, PS>), dim3(mb, (unsigned)g.count), dim3(P * TP), (z4_lds<M, TP, PS>()),
-                     st, g);
+  hipLaunchKernelGGL((k_zsolve4_grp<M, TP, PS>), dim3(nb), dim3(P * TP), (z4_lds<M, TP, PS>()), st, g);
   return hipGetLastError();
 }
 // the smallest layout that holds P chunks: F<M, TP, PS>

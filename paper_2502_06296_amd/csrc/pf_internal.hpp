@@ -461,6 +461,7 @@ hipError_t launch_xinv_grp(int nx, GJobs &g, hipStream_t st);
 // every job of the group runs z-solve `variant` (a separator-form shape)
 // with the same chunk count
 hipError_t launch_zsolve_grp(int variant, GJobs &g, hipStream_t st);
+void z_group_shares(long resident, int count, const long *tiles, unsigned *share);
 bool zsolve_variant_groups(int variant);
 int zsolve_chunks(int variant, int nz);  // P of a variant for nz rows
 // Helmholtz apply (Algorithm 2, Steps 2-4).

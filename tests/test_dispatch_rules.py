@@ -92,3 +92,21 @@ X_LINES = [
 def test_x_transform_lines_are_the_faster_ones(case, lines):
     rule = _rule("_ZN2pf7x_linesEibil", C.c_int, C.c_bool, C.c_int, C.c_long)
     assert rule(*case) == lines
+
+
+@pytest.mark.parametrize("resident,tiles", [
+    (512, [13 * 192, 9 * 128, 5 * 64]), (256, [17 * 256, 13 * 96, 9 * 64, 5 * 64, 17 * 192]), (1024, [300, 200, 500]),
+    (256, [100000] + [64] * 15), (512, [1] * 16), (256, [4000] * 16)])
+def test_grouped_persistent_shares_fit_one_round(resident, tiles):
+    fn = N.lib()._ZN2pf14z_group_sharesEliPKlPj
+    fn.restype = None
+    n = len(tiles)
+    share = (C.c_uint * n)()
+    fn(C.c_long(resident), C.c_int(n), (C.c_long * n)(*tiles), share)
+    assert sum(share) <= resident
+    assert all(1 <= s <= t for s, t in zip(share, tiles))
+    # nothing is left over, and no workgroup has more than one tile above the
+    # even split of what the jobs of one workgroup leave
+    assert sum(share) == min(resident, sum(tiles))
+    even = -(-sum(tiles) // (resident - n))
+    assert max(-(-t // s) for s, t in zip(share, tiles)) <= even + 1
