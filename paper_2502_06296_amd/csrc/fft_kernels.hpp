@@ -439,6 +439,10 @@ __device__ __forceinline__ void plane_mean(const PlaneMean &pm, int k, int rows)
   for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
   if (threadIdx.x == 0) pm.out[k] = pm.m ? pm.m[k] - a * pm.inv : a * pm.inv;
 }
+// the means of a persistent launch's share of the planes
+__device__ __forceinline__ void plane_means(const PlaneMean &pm, int planes, int rows) {
+  for (int k = blockIdx.x; k < planes; k += gridDim.x) plane_mean(pm, k, rows);
+}
 
 template <typename T, int N, int TPL, int LPW, int YW, bool XR = false, int RO = 0>
 __device__ __forceinline__ void yfwd_body(T *__restrict__ data,
@@ -613,6 +617,7 @@ __global__ __launch_bounds__(TPL *LPW) void k_y_persist(T *__restrict__ data,
   const int l = tid % LPW, t = tid / LPW;
   C *buf = lds + l * y_stride(N);
   const long G = gridDim.x;
+  if (!INV) plane_means(pm, (int)(nblk / nib), N);  // before the walk, whose registers it would add to
   long blk = pf_round_block(0, G, nblk);
   if (blk >= nblk) return;  // uniform
   auto at = [&](long b) { return data + (size_t)(b / nib) * sp + (size_t)(b % nib) * 2 * LPW; };
@@ -627,7 +632,6 @@ __global__ __launch_bounds__(TPL *LPW) void k_y_persist(T *__restrict__ data,
   for (long i = 0;; ++i) {
     const int ib = (int)(blk % nib);
     T *base = at(blk);
-    if (!INV && ib == 0) plane_mean(pm, (int)(blk / nib), N);
     const long nb = pf_round_block(i + 1, G, nblk);
     const bool more = nb < nblk;  // uniform
     // the thread's positions as values the compiler cannot carry from one

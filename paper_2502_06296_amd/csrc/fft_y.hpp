@@ -35,7 +35,10 @@ constexpr bool yr_unpair(int n) {
   return n != 192 && n != 384 && n != 2048 && n != 3200 && (n != 3456 || sizeof(T) == 8);
 }
 
-template <typename T, int N, int LPW, bool INV, int YW, bool XR>
+// WALK: one of many blocks of a persistent workgroup. The thread's number is then
+// made anew for each block, or the compiler keeps every address of the passes
+// across the loop (up to 139 registers spilled).
+template <typename T, int N, int LPW, bool INV, int YW, bool XR, bool WALK = false>
 __device__ __forceinline__ void yr_body(T *data, const cplx<double> *__restrict__ tw,
                                         const cplx<double> *__restrict__ ctw, int nx, int nib, size_t sp,
                                         const PlaneMean &pm, unsigned bx_, unsigned gx_) {
@@ -44,7 +47,9 @@ __device__ __forceinline__ void yr_body(T *data, const cplx<double> *__restrict_
   constexpr int NT = L::tpl * LPW, S = rx_stride(N, LPW);
   static_assert(NT >= 64, "a whole wave takes the plane mean");
   __shared__ double lds[LPW * S];
-  const int tid = threadIdx.x, l = tid % LPW, t = tid / LPW;
+  int tid = threadIdx.x;
+  if constexpr (WALK) asm volatile("" : "+v"(tid));
+  const int l = tid % LPW, t = tid / LPW;
   const unsigned blk = xcd_block(bx_, gx_);
   const int ib = blk % nib;
   const long k = blk / nib;
@@ -242,13 +247,16 @@ __global__ __launch_bounds__(LinePlan<N>::tpl *LPW) void k_yr(T *data, const cpl
   yr_body<T, N, LPW, INV, YW, XR>(data, tw, ctw, nx, nib, sp, pm, blockIdx.x, gridDim.x);
 }
 // The same for a grid of at most one round of resident workgroups, which
-// walk the blocks; nothing of a block outlives its turn.
+// walk the blocks; nothing of a block outlives its turn, and nothing is loaded
+// ahead. The plane means come before the walk, whose registers they would add
+// to.
 template <typename T, int N, int LPW, bool INV>
 __global__ __launch_bounds__(LinePlan<N>::tpl *LPW) void k_yr_persist(T *data, const cplx<double> *__restrict__ tw,
                                                                        int nx, int nib, size_t sp, unsigned nblk,
                                                                        PlaneMean pm) {
+  if (!INV) plane_means(pm, (int)(nblk / nib), N);
   for (unsigned b = blockIdx.x; b < nblk; b += gridDim.x) {  // uniform
-    yr_body<T, N, LPW, INV, 0, false>(data, tw, nullptr, nx, nib, sp, pm, b, nblk);
+    yr_body<T, N, LPW, INV, 0, false, true>(data, tw, nullptr, nx, nib, sp, PlaneMean{}, b, nblk);
     __syncthreads();
   }
 }
