@@ -10,9 +10,10 @@ variants for the stages that have more than one:
 * the Helmholtz apply (rows per chunk, columns per chunk).
 
 Winners are kept in a JSON cache keyed by GPU architecture, HIP runtime
-version, shape and precision (path: $PF_TUNE_CACHE, else
-~/.cache/pf_channel/tune.json). A corrupt or unreadable cache is ignored.
-poisson_plan applies a cached entry for its shape and precision by default
+version, the library's table of shapes, shape, precision and boundaries (path:
+$PF_TUNE_CACHE, else ~/.cache/pf_channel/tune.json). A corrupt or unreadable
+cache is ignored, and so are entries of another table, whose numbers stand for
+other kernels. poisson_plan applies a cached entry for its grid and precision by default
 (apply_cached_poisson). Tuning runs kernels and may allocate; do it at
 set-up, not inside a graph capture.
 """
@@ -24,6 +25,9 @@ import os
 
 from . import _native as N
 from . import solver
+
+# raised whenever a shape number comes to stand for another kernel
+SHAPE_TABLE = 2
 
 STAGE_XFWD = 0
 STAGE_YFWD = 1
@@ -38,7 +42,7 @@ def cache_path():
 def _arch_key():
     import torch
     p = torch.cuda.get_device_properties(torch.cuda.current_device())
-    return f"{getattr(p, 'gcnArchName', p.name)}|hip{torch.version.hip}"
+    return f"{getattr(p, 'gcnArchName', p.name)}|hip{torch.version.hip}|shapes{SHAPE_TABLE}"
 
 
 def load_cache(path=None):
@@ -192,8 +196,13 @@ def tune_pcr(plans, fields, reps=3):
     return times
 
 
-def poisson_key(nx, ny, nz, precision):
-    return f"{_arch_key()}|poisson|{nx}x{ny}x{nz}|{precision}"
+def poisson_key(nx, ny, nz, precision, ybc=0, xbc=0):
+    walls = f"|y{ybc}x{xbc}" if ybc or xbc else ""
+    return f"{_arch_key()}|poisson|{nx}x{ny}x{nz}|{precision}{walls}"
+
+
+def _plan_key(plan, nx, ny, nz, precision):
+    return poisson_key(nx, ny, nz, precision, getattr(plan, "ybc", 0), getattr(plan, "xbc", 0))
 
 
 def pcr_key(n, nx, ny, precision, count):
@@ -202,10 +211,11 @@ def pcr_key(n, nx, ny, precision, count):
 
 def apply_cached_poisson(plan, nx, ny, nz, precision, path=None):
     """Apply the cached variants (z solve, x and y transform shapes) for this
-    shape and precision if the cache holds an entry that fits the plan.
+    shape, precision and the plan's boundaries if the cache holds an entry that
+    fits the plan.
     Returns the applied entry or None."""
     try:
-        ent = load_cache(path).get(poisson_key(nx, ny, nz, precision))
+        ent = load_cache(path).get(_plan_key(plan, nx, ny, nz, precision))
     except Exception:  # no device properties (or no torch): nothing to apply
         return None
     if not isinstance(ent, dict):
@@ -222,7 +232,7 @@ def apply_or_tune_poisson(plan, rhs, p, precision, reps=3, path=None):
     """Use the cached variants for this shape, or tune the z solve and the
     transform shapes and cache them."""
     nz, ny, nx = plan.shape
-    key = poisson_key(nx, ny, nz, precision)
+    key = _plan_key(plan, nx, ny, nz, precision)
     cache = load_cache(path)
     ent = cache.get(key) if isinstance(cache.get(key), dict) else {}
     if "zsolve_variant" in ent and "xshape" in ent and "yshape" in ent:

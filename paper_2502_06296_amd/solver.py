@@ -46,6 +46,8 @@ def zop_rows(nz, bc, lz=2.0, beta=1.5, zf=None):
 
 
 class PoissonPlan:
+    ybc = xbc = 0  # boundaries: periodic
+
     def __init__(self, handle, shape, precision, stream, workspace):
         self.handle = handle
         self.shape = shape
@@ -83,6 +85,7 @@ def poisson_plan(nx, ny, nz, lx=6.283185307179586, ly=3.141592653589793, lz=2.0,
         N.check(N.lib().poisson_plan(C.byref(h), C.byref(g), _prec(precision), int(n_refine), s,
                                      C.byref(ws)))
         plan = PoissonPlan(h, (nz, ny, nx), _prec(precision), stream, None)
+        plan.ybc, plan.xbc = yb, xb
         if ws.value:
             plan.workspace = torch.empty(ws.value, dtype=torch.uint8, device=dev)
             N.check(N.lib().poisson_set_workspace(h, _ptr(plan.workspace), ws.value))
