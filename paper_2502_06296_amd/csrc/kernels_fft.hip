@@ -229,16 +229,23 @@ hipError_t launch_status_final(unsigned long long *stat, double tol, bool refine
 }
 
 // Periodic x: the lengths that are faster on the register engine there.
+template <typename T, int N, int LPW>
+hipError_t xr_div_launch(const DivArgs &d, T *out, const cplx<double> *tw, double *sums, long ncl, int ny, int nz,
+                         size_t sp, hipStream_t st) {
+  const dim3 g((unsigned)((ncl + LPW - 1) / LPW)), b(LinePlan<N>::tpl * LPW);
+  if (d.stash)
+    hipLaunchKernelGGL((k_xr_div<T, N, LPW, true>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
+  else
+    hipLaunchKernelGGL((k_xr_div<T, N, LPW, false>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
+  return hipGetLastError();
+}
 template <typename T, int N>
 hipError_t xfwd_div_periodic(const DivArgs &d, T *out, const cplx<double> *tw, double *sums, long ncl, int ny, int nz,
                              size_t sp, hipStream_t st) {
   if constexpr (x_div_in_regs(N)) {
-    constexpr int LPW = xr_lpw(N);
-    const dim3 g((unsigned)((ncl + LPW - 1) / LPW)), b(LinePlan<N>::tpl * LPW);
-    if (d.stash)
-      hipLaunchKernelGGL((k_xr_div<T, N, LPW, true>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
-    else
-      hipLaunchKernelGGL((k_xr_div<T, N, LPW, false>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
+    if (x_lines(kXDivergence, sizeof(T) == 8, N, ncl) == xr_lpw(N))
+      return xr_div_launch<T, N, xr_lpw(N)>(d, out, tw, sums, ncl, ny, nz, sp, st);
+    return xr_div_launch<T, N, xr_div_half(N)>(d, out, tw, sums, ncl, ny, nz, sp, st);
   } else {
     constexpr int TPL = xfwd_tpl(N), LPW = x_lpw(N);
     const dim3 g((unsigned)((ncl + LPW - 1) / LPW)), b(TPL * LPW);
@@ -246,8 +253,8 @@ hipError_t xfwd_div_periodic(const DivArgs &d, T *out, const cplx<double> *tw, d
       hipLaunchKernelGGL((k_xfwd_div<T, N, TPL, LPW, true>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
     else
       hipLaunchKernelGGL((k_xfwd_div<T, N, TPL, LPW, false>), g, b, 0, st, d, out, tw, sums, ncl, ny, nz, sp);
+    return hipGetLastError();
   }
-  return hipGetLastError();
 }
 
 template <typename T>
@@ -347,6 +354,8 @@ __global__ __launch_bounds__(TPL *LPW) void k_xinv_grp(const GJobs g) {
 // engine
 int x_lines(int pass, bool fp64, int n, long pairs) {
   if (pass == kXResidual) return resid_in_regs(n) ? xr_resid_lpw(n) : 0;
+  if (pass == kXDivergence)
+    return !x_div_in_regs(n) ? 0 : pairs <= 1024l * xr_lpw(n) ? xr_div_half(n) : xr_lpw(n);
   const bool regs = pass == kXForward ? (fp64 ? x_fwd_in_regs<double>(n) : x_fwd_in_regs<float>(n))
                                       : (fp64 ? x_inv_in_regs<double>(n) : x_inv_in_regs<float>(n));
   if (!regs) return 0;

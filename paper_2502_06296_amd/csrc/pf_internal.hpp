@@ -209,17 +209,21 @@ constexpr bool resid_in_regs(int n) { return n == 256 || n == 512 || n >= 2048; 
 // workgroups would leave half the compute units without one (1024 float32
 // points on 2^20 values: forward 10.0 against 8.6 us, inverse 9.6 / 8.5). The residual's
 // divide ny, which is a multiple of 16; 4 are faster than 8 for 256 and 512
-// points (2^26 values 0.305 / 0.281 and 0.262 / 0.256 ms).
+// points (2^26 values 0.305 / 0.281 and 0.262 / 0.256 ms). The divergence pass of
+// 512, 1024 and 2048 points takes half the pairs up to 1024 workgroups of all of
+// them (512 points on 2^22 values 36 / 28 us, 1024 points 33 / 29, on the LDS
+// engine 33; 2048 points on 2^24 values 136 / 145).
 constexpr int xr_lpw(int n) {
   int v = 1;
   while (2 * v * (n / 16) <= 256) v *= 2;
   return v;
 }
 constexpr int xr_half(int n) { return xr_lpw(n) < 2 ? 1 : xr_lpw(n) / 2; }
+constexpr int xr_div_half(int n) { return n == 512 || n == 1024 || n == 2048 ? xr_half(n) : xr_lpw(n); }
 constexpr int xr_resid_lpw(int n) { return xr_lpw(n) > 4 ? 4 : xr_lpw(n); }
 // What these rules choose for `pairs` line pairs of n points: line pairs per
 // workgroup of the register engine, 0 for the LDS engine.
-enum : int { kXForward = 0, kXInverse = 1, kXResidual = 2 };
+enum : int { kXForward = 0, kXInverse = 1, kXResidual = 2, kXDivergence = 3 };
 int x_lines(int pass, bool fp64, int n, long pairs);
 
 // Launch shapes of the periodic transforms the autotuner chooses from, per

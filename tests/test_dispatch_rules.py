@@ -75,7 +75,7 @@ def test_y_transform_lines_are_the_faster_ones(case, lines):
 
 # (pass, float64, points, line pairs), the line pairs of a workgroup of the
 # register engine, 0 for the LDS engine
-FWD, INV, RESID = 0, 1, 2
+FWD, INV, RESID, DIV = 0, 1, 2, 3
 X_LINES = [
     ((FWD, False, 256, 1 << 16), 0), ((FWD, False, 512, 1 << 18), 0), ((FWD, False, 768, 1 << 16), 4),
     ((FWD, True, 1024, 1 << 17), 0), ((FWD, True, 2048, 1 << 15), 0), ((FWD, True, 3072, 1 << 15), 0),
@@ -83,6 +83,8 @@ X_LINES = [
     ((FWD, False, 1024, 513), 4), ((FWD, False, 1024, 512), 2), ((FWD, False, 3200, 100), 1),
     ((INV, False, 512, 1 << 18), 0), ((INV, False, 384, 1 << 16), 8), ((INV, False, 2048, 200), 1),
     ((INV, True, 2048, 1 << 15), 0), ((INV, True, 3456, 1 << 15), 1),
+    ((DIV, True, 192, 1 << 14), 0), ((DIV, True, 512, 1 << 12), 4), ((DIV, True, 512, 1 << 14), 8),
+    ((DIV, False, 1024, 1 << 11), 2), ((DIV, True, 1024, 1 << 14), 4), ((DIV, True, 768, 1 << 11), 4),
     ((RESID, False, 384, 1 << 14), 0), ((RESID, False, 512, 1 << 17), 4), ((RESID, False, 768, 1 << 14), 0),
     ((RESID, False, 1024, 1 << 17), 0), ((RESID, False, 1536, 1 << 16), 0), ((RESID, False, 2048, 1 << 15), 2),
 ]
