@@ -276,9 +276,9 @@ pf_status helmholtz3d_update(pf_poisson_plan *plan, double s);
  * for it; pcr_update_coef reruns it).
  * precision: PF_FP64 (float64 field), PF_FP32 (float32 field), or
  * PF_FP32_REFINE (float64 field, float32 solves plus one float64-residual
- * correction in registers; where the chunks are of 32 rows, n > 256 unless
- * tuned, or narrower than a wave, one float64 elimination instead, which is
- * the faster there and the more accurate). n >= 4. */
+ * correction in registers; where the chunks are narrower than a wave, n >
+ * 512 unless tuned, one float64 elimination instead, which is the faster
+ * there and the more accurate). n >= 4. */
 pf_status pcr_prepare(pf_pcr_plan **out, int32_t n, const double *alpha, const double *gamma,
                       const double *excess, double s, int32_t precision, int32_t chunk_rows,
                       void *stream);

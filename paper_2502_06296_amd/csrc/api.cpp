@@ -1277,17 +1277,16 @@ struct HelmGroup {
   int count = 0;
 };
 
-// The arithmetic of a plan's apply (launch_helm's precision). A refined plan of
-// 32-row chunks (by default columns of more than 256 rows), or of chunks
-// narrower than a wave, eliminates once in float64: both move the same float64
-// field, and the float32 solve, its float64 residual and the second solve do
-// not fit the registers beside the 32 rows of a chunk (three fields at
-// 1024x1024x1024: 14.77 ms with half the rows parked in LDS, 11.34 in float64;
-// 512x512x300 0.847 against 0.799 ms, 256x256x512 0.338 / 0.329, 512x512x512
-// 1.38 / 1.39; an error of 1e-16 instead of 3e-15). Fields of 513 and 512 rows
-// (u and w of a channel) so share a launch.
+// The arithmetic of a plan's apply (launch_helm's precision). A refined plan
+// whose chunks are narrower than a wave (columns of more than 512 rows)
+// eliminates once in float64: both move the same float64 field, and the
+// float32 solve, its float64 residual and the second solve do not fit the
+// registers beside the 32 rows of a chunk (three fields at 1024x1024x1024:
+// 14.77 ms with half the rows parked in LDS, 11.34 in float64, and an error of
+// 1e-16 instead of 3e-15). Up to 512 rows the refined solves are as fast
+// (512x384x256 0.463 against 0.493 ms).
 static int helm_mode(const pf_pcr_plan *pl) {
-  if (pl->prec == PF_FP32_REFINE) return (pl->cw < 64 || pl->M == 32) && !pl->staged ? 0 : 2;
+  if (pl->prec == PF_FP32_REFINE) return pl->cw < 64 && !pl->staged ? 0 : 2;
   return pl->prec == PF_FP64 ? 0 : 1;
 }
 

@@ -1507,7 +1507,7 @@ __device__ __forceinline__ void helm_column(TS *cp, size_t plane, int r0, int n,
       }
     }
   } else {
-    static_assert(CW == 64 && M <= 16, "the other chunks eliminate in float64");
+    static_assert(CW == 64, "narrower chunks eliminate in float64");
     // the float64 right-hand side is held in registers for the residual
     double r[M];
     TC u[M], dd[M];
@@ -1546,11 +1546,11 @@ __device__ __forceinline__ void helm_column(TS *cp, size_t plane, int r0, int n,
 // CW columns per chunk: 64 (one wave per chunk, wave-uniform coefficient
 // addresses), 32 or 16 (two or four chunks per wave, so that a column of 32
 // chunks fits a workgroup; the Step 1 tables are then copied to LDS after
-// the reduced rows: 5 P M values of TC). REFINE has 64 and chunks of up to 16
-// rows only: other columns are eliminated once in float64 instead, because two
-// float32 solves and the residual between them do not fit the registers of 32
-// rows a thread (1024x1024x1024, three components: 14.8 ms refined with half
-// the rows parked in LDS, 11.0 ms in float64; 512x512x300 0.85 and 0.80).
+// the reduced rows: 5 P M values of TC). REFINE has 64 only: a column of more
+// than 512 rows is eliminated once in float64 instead, because two float32
+// solves and the residual between them do not fit the registers of the 1024
+// threads that such a column takes (1024x1024x1024, three components: 14.8 ms
+// refined with half the rows parked in LDS, 11.0 ms in float64).
 template <typename TS, typename TC, int M, int CW, bool REFINE>
 __global__ __launch_bounds__(1024) void k_helm(HelmArgs args) {
   extern __shared__ double shd[];
@@ -1811,7 +1811,7 @@ hipError_t launch_helm(int precision, int chunk_rows, int cw, bool staged, int c
   dim3 g((unsigned)maxblk, (unsigned)count), b(CW * maxP);
   // the reduced rows: one float64 array, or two float32 arrays (refinement);
   // chunks narrower than a wave add the Step 1 tables (see k_helm)
-  if (precision == 2 && (CW < 64 || chunk_rows > 16)) return hipErrorInvalidValue;
+  if (precision == 2 && CW < 64) return hipErrorInvalidValue;
   size_t shm = (size_t)2 * maxP * CW * sizeof(double);
   if (CW < 64) shm += (size_t)maxP * chunk_rows * 5 * (precision == 0 ? 8 : 4);
   if (shm > 160 * 1024) return hipErrorInvalidValue;
@@ -1820,7 +1820,7 @@ hipError_t launch_helm(int precision, int chunk_rows, int cw, bool staged, int c
     hipLaunchKernelGGL((k_helm<double, double, M, CWV, false>), g, b, shm, st, a);              \
   else if (precision == 1)                                                                      \
     hipLaunchKernelGGL((k_helm<float, float, M, CWV, false>), g, b, shm, st, a);                \
-  else if constexpr (CWV == 64 && M <= 16)                                                      \
+  else if constexpr (CWV == 64)                                                                 \
     hipLaunchKernelGGL((k_helm<double, float, M, CWV, true>), g, b, shm, st, a);
 #define PF_HELM(M)                    \
   case M:                             \
