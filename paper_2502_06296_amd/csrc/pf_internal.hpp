@@ -169,18 +169,18 @@ constexpr bool y_lds_mode(int n, bool inv, int yw, bool xr) {
   return false;
 }
 // The LDS engine up to this many workgroups (of the register engine), where it
-// is the faster one on small fields: periodic float64 lines while the field
-// stays in the last-level cache (2^22 values of 1024 points 17 against 19 us;
-// 2048 points on 2^24 54 / 67, but on 2^26 0.32 / 0.26 ms), faces (256 rows
-// of float32 on 2^21 values 13 / 15 us, on 2^23 31 / 29), the long inverses behind x walls (3072
-// points on 2^21 values 16 / 18), the walls' forward of 192 and 256 points
-// (2^22 values 12 / 13.5, but on 2^26 121 / 110).
+// is the faster one on small fields: faces (256 rows of float32 on 2^21 values
+// 13 / 15 us, on 2^23 31 / 29), the long inverses behind x walls (3072 points on
+// 2^21 values 16 / 18), the walls' forward of 192 and 256 points (2^22 values 12
+// / 13.5, but on 2^26 121 / 110). Periodic float64 lines of 1024-2048 points
+// would be faster there on a field alone in the last-level cache (2048 points
+// on 2^24 values 54 / 67), but not beside a projection's other fields (192 x
+// 2048 x 40: substep 0.740 / 0.718 ms).
 template <typename T>
 constexpr long y_lds_wgs(int n, bool inv, int yw, bool xr) {
   if (yw == 3) return n == 768 ? 192 : n <= 1024 ? 352 : 0;
   if (xr && inv) return 128;
-  if (sizeof(T) == 4) return n <= 256 && !inv && (yw || xr) ? 512 : 0;
-  return yw == 0 && !xr && n <= 2048 ? (n == 768 ? 192 : 1024) : 0;
+  return sizeof(T) == 4 && n <= 256 && !inv && (yw || xr) ? 512 : 0;
 }
 // What these rules choose for nx slots and nz planes of n points: lines per
 // workgroup of the register engine, 0 for the LDS engine.

@@ -52,8 +52,9 @@ Y_LINES = [
     ((True, 768, True, 0, False, 1024, 512), 8),
     # 48 slots
     ((False, 256, False, 1, False, 48, 1000), 8), ((False, 512, False, 1, False, 48, 512), 8),
-    # cached float64 lines; walls of the same size
-    ((True, 1024, False, 0, False, 512, 32), 0), ((True, 2048, True, 0, False, 512, 16), 0),
+    # cached float64 lines
+    ((True, 1024, False, 0, False, 512, 32), 8), ((True, 2048, True, 0, False, 192, 40), 4),
+    ((True, 2048, True, 0, False, 64, 16), 2), ((True, 1536, False, 0, False, 512, 30), 8),
     ((True, 1024, False, 0, False, 1024, 512), 8), ((True, 2048, True, 0, False, 1024, 128), 4),
     ((True, 1024, False, 1, False, 512, 32), 8), ((True, 2048, True, 1, False, 512, 16), 4),
     # faces, and the inverse behind x walls
