@@ -192,9 +192,12 @@ int y_lines(bool fp64, int n, bool inv, int yw, bool xr, int nx, int nz);
 // LDS engine (512 x 512 x 512 0.298 against 0.312 ms, 1024 x 512 x 512 float64
 // 0.757 / 0.771, 2048 x 1024 x 256 1.50 / 1.53, 3072 points on 2^26 values
 // 0.202 / 0.214), the inverse 512 float32 points (0.383 / 0.403 ms) and the
-// float64 powers of two (1024 x 512 x 512 0.769 / 0.824), the residual 384, 768,
-// 1024 and 1536 points (384 points on 2^23 values 32 / 35 us, 768 on 2^24
-// 55 / 61, 1024 x 512 x 512 1.05 / 1.08 ms, 1536 x 512 x 256 0.845 / 0.920).
+// float64 powers of two (1024 x 512 x 512 0.769 / 0.824), the residual 1536
+// points (1536 x 512 x 256 0.845 / 0.920). The residual of 384, 768 and 1024
+// points is a little faster there too on small fields (768 on 2^24 values 55 /
+// 61 us, 1024 on 2^22 20 / 22; 1024 x 512 x 512 1.05 / 1.07 ms), but another
+// engine's roundings move the correction pressure of a field that a projection
+// has already made divergence-free, which is nothing but rounding.
 template <typename T>
 constexpr bool x_fwd_in_regs(int n) {
   return sizeof(T) == 8 ? n == 1536 || n > 3072 : n >= 384 && n != 512;
@@ -204,7 +207,7 @@ constexpr bool x_inv_in_regs(int n) {
   return sizeof(T) == 8 ? n > 2048 || n == 1536 : n >= 768 || n == 384;
 }
 constexpr bool x_div_in_regs(int n) { return n >= 256; }
-constexpr bool resid_in_regs(int n) { return n == 256 || n == 512 || n >= 2048; }
+constexpr bool resid_in_regs(int n) { return n >= 256 && n != 1536; }
 // Line pairs per workgroup: about 256 threads; half of that where all the
 // workgroups would leave half the compute units without one (1024 float32
 // points on 2^20 values: forward 10.0 against 8.6 us, inverse 9.6 / 8.5). The residual's
@@ -220,7 +223,7 @@ constexpr int xr_lpw(int n) {
 }
 constexpr int xr_half(int n) { return xr_lpw(n) < 2 ? 1 : xr_lpw(n) / 2; }
 constexpr int xr_div_half(int n) { return n == 512 || n == 1024 || n == 2048 ? xr_half(n) : xr_lpw(n); }
-constexpr int xr_resid_lpw(int n) { return xr_lpw(n) > 4 ? 4 : xr_lpw(n); }
+constexpr int xr_resid_lpw(int n) { return n == 256 || n == 512 ? 4 : xr_lpw(n) > 8 ? 8 : xr_lpw(n); }
 // What these rules choose for `pairs` line pairs of n points: line pairs per
 // workgroup of the register engine, 0 for the LDS engine.
 enum : int { kXForward = 0, kXInverse = 1, kXResidual = 2, kXDivergence = 3 };

@@ -86,8 +86,8 @@ X_LINES = [
     ((INV, True, 2048, 1 << 15), 0), ((INV, True, 3456, 1 << 15), 1),
     ((DIV, True, 192, 1 << 14), 0), ((DIV, True, 512, 1 << 12), 4), ((DIV, True, 512, 1 << 14), 8),
     ((DIV, False, 1024, 1 << 11), 2), ((DIV, True, 1024, 1 << 14), 4), ((DIV, True, 768, 1 << 11), 4),
-    ((RESID, False, 384, 1 << 14), 0), ((RESID, False, 512, 1 << 17), 4), ((RESID, False, 768, 1 << 14), 0),
-    ((RESID, False, 1024, 1 << 17), 0), ((RESID, False, 1536, 1 << 16), 0), ((RESID, False, 2048, 1 << 15), 2),
+    ((RESID, False, 384, 1 << 14), 8), ((RESID, False, 512, 1 << 17), 4), ((RESID, False, 768, 1 << 14), 4),
+    ((RESID, False, 1024, 1 << 17), 4), ((RESID, False, 1536, 1 << 16), 0), ((RESID, False, 2048, 1 << 15), 2),
 ]
 
 
