@@ -1283,8 +1283,11 @@ struct HelmGroup {
 // float32 solve, its float64 residual and the second solve do not fit the
 // registers beside the 32 rows of a chunk (three fields at 1024x1024x1024:
 // 14.77 ms with half the rows parked in LDS, 11.34 in float64, and an error of
-// 1e-16 instead of 3e-15). Up to 512 rows the refined solves are as fast
-// (512x384x256 0.463 against 0.493 ms).
+// 1e-16 instead of 3e-15). Up to 512 rows the refined solves stay; float64
+// takes 0.94 of their time at 300 rows and as much at 512 (512x512 planes: 0.847
+// against 0.799 ms, 1.38 / 1.39), but other roundings in the velocities move the
+// correction pressure of a field that a projection has already made
+// divergence-free.
 static int helm_mode(const pf_pcr_plan *pl) {
   if (pl->prec == PF_FP32_REFINE) return pl->cw < 64 && !pl->staged ? 0 : 2;
   return pl->prec == PF_FP64 ? 0 : 1;
@@ -1320,10 +1323,26 @@ static pf_status pcr_group(int32_t count, pf_pcr_plan *const *plans, void *const
   return PF_OK;
 }
 
+// A refined group of 32-row chunks of both kinds, in the default widths, on
+// planes of up to 65536 columns; larger ones fill the chip in a launch of each
+// kind (512x512x513 1.58 against 1.62 ms in one).
+static bool helm_mixed(const HelmGroup &G, unsigned &wide) {
+  wide = 0;
+  for (int t = 0; t < G.count; ++t) {
+    const pf_pcr_plan *p = G.plans[t];
+    if (p->prec != PF_FP32_REFINE || p->M != 32 || p->staged || (p->cw != 64 && p->cw != 32)) return false;
+    if ((long)G.jobs[t].nx * G.jobs[t].ny > 65536) return false;
+    if (helm_mode(p) == 2) wide |= 1u << t;
+  }
+  return wide && wide != (1u << G.count) - 1;
+}
+
 // One launch for the fields that share a kernel: one for the whole group,
-// unless its chunks are of different kinds.
+// unless its chunks are of different kinds in tuned shapes.
 static pf_status pcr_enqueue(pf_pcr_plan *p0, const HelmGroup &G, hipStream_t st) {
   return run_stage(p0->tm, st, PF_STAGE_PCR_APPLY, [&]() {
+    unsigned wide = 0;
+    if (helm_mixed(G, wide)) return pf::launch_helm_mixed(G.count, G.jobs, wide, st);
     bool done[pf::kMaxHelmJobs] = {};
     for (int first = 0; first < G.count; ++first) {
       if (done[first]) continue;

@@ -1477,6 +1477,7 @@ __device__ __forceinline__ void helm_solve_regs(TC (&d)[M], RW fa, RW bg, RW ib,
 struct HelmArgs {
   HelmJob job[kMaxHelmJobs];
   int count;
+  unsigned wide;  // k_helm_mixed
 };
 
 // Steps 2-4 for the chunk of one lane (see k_helm), with the Step 1 rows
@@ -1552,9 +1553,8 @@ __device__ __forceinline__ void helm_column(TS *cp, size_t plane, int r0, int n,
 // threads that such a column takes (1024x1024x1024, three components: 14.8 ms
 // refined with half the rows parked in LDS, 11.0 ms in float64).
 template <typename TS, typename TC, int M, int CW, bool REFINE>
-__global__ __launch_bounds__(1024) void k_helm(HelmArgs args) {
+__device__ __forceinline__ void helm_body(const HelmJob &J) {
   extern __shared__ double shd[];
-  const HelmJob &J = args.job[blockIdx.y];
   const HelmCoef &C = J.c;
   const int nib = J.nx / CW;
   const long nblk = (long)nib * J.ny;
@@ -1599,6 +1599,18 @@ __global__ __launch_bounds__(1024) void k_helm(HelmArgs args) {
     helm_column<TS, TC, M, REFINE, CW>(cp, plane, r0, C.n, R{fa, r0}, R{bg, r0}, R{ibv, r0}, R{ra, r0},
                                        R{rc, r0}, mal, mga, mdg, tf, tb, ti, C.P, RD, w, lane, active);
   }
+}
+template <typename TS, typename TC, int M, int CW, bool REFINE>
+__global__ __launch_bounds__(1024) void k_helm(HelmArgs args) {
+  helm_body<TS, TC, M, CW, REFINE>(args.job[blockIdx.y]);
+}
+// Refined plans of 32-row chunks of both kinds in one launch: the jobs of args.wide
+// refine in 64-column chunks, the others eliminate in float64 in 32-column ones
+// (u, v and w of a channel of 513 rows, 513, 513 and 512 unknowns: two launches
+// on a 64 x 8 plane took 28 us, one 16.5).
+__global__ __launch_bounds__(1024) void k_helm_mixed(HelmArgs args) {
+  if (args.wide >> blockIdx.y & 1u) helm_body<double, float, 32, 64, true>(args.job[blockIdx.y]);
+  else helm_body<double, double, 32, 32, false>(args.job[blockIdx.y]);
 }
 
 // Same algorithm, coefficient tables staged in LDS. A persistent workgroup
@@ -1754,6 +1766,27 @@ size_t helm_lds_bytes(int precision, int M, int P, int steps, int CW) {
 }
 
 int helm_default_cw(int P) { return P <= 16 ? 64 : 32; }
+
+hipError_t launch_helm_mixed(int count, const HelmJob *jobs, unsigned wide, hipStream_t st) {
+  if (count < 1 || count > kMaxHelmJobs) return hipErrorInvalidValue;
+  HelmArgs a;
+  a.count = count;
+  a.wide = wide;
+  long blocks = 0;
+  int threads = 0;
+  size_t shm = 0;
+  for (int t = 0; t < count; ++t) {
+    a.job[t] = jobs[t];
+    const int cw = wide >> t & 1u ? 64 : 32, P = jobs[t].c.P;
+    if (P < 1 || P * cw > 1024 || jobs[t].nx % cw) return hipErrorInvalidValue;
+    blocks = std::max(blocks, (long)(jobs[t].nx / cw) * jobs[t].ny);
+    threads = std::max(threads, P * cw);
+    // reduced rows; narrow chunks add the float64 Step 1 tables (see k_helm)
+    shm = std::max(shm, (size_t)2 * P * cw * sizeof(double) + (cw < 64 ? (size_t)P * 32 * 5 * 8 : 0));
+  }
+  hipLaunchKernelGGL(k_helm_mixed, dim3((unsigned)blocks, (unsigned)count), dim3(threads), shm, st, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_helm(int precision, int chunk_rows, int cw, bool staged, int count,
                        const HelmJob *jobs, hipStream_t st) {

@@ -493,6 +493,9 @@ constexpr int kMaxHelmJobs = 16;  // fields of one grouped Helmholtz launch
 // staged: persistent workgroups with the Step 1 tables in LDS.
 hipError_t launch_helm(int precision, int chunk_rows, int cw, bool staged, int count,
                        const HelmJob *jobs, hipStream_t st);
+// Refined jobs of 32-row chunks, those of the bits of `wide` in 64-column chunks
+// (precision 2 above), the others in 32-column chunks in float64 (precision 0).
+hipError_t launch_helm_mixed(int count, const HelmJob *jobs, unsigned wide, hipStream_t st);
 int helm_default_cw(int P);
 
 // Algorithm 2, Step 1 on the device: from the rows (alpha, gamma, excess)
