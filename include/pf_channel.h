@@ -224,7 +224,7 @@ pf_status poisson_project(pf_poisson_plan *plan, double *u, double *v, double *w
  * float64-residual correction (PF_FP32_REFINE), periodic in x and y, whose
  * z solve takes a separator-form shape (the default for every supported
  * size), run grouped: each stage of all of them is one launch per kernel
- * instance (one per transform length; per z-solve shape and chunk count),
+ * instance (one per transform length; per z-solve shape and row count),
  * at most 16 problems a launch; the other plans run one after another
  * afterwards. Results equal poisson_solve's bitwise. Stage timing, when
  * enabled on the first grouped plan, records the grouped launches there.

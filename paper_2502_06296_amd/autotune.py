@@ -6,15 +6,16 @@ variants for the stages that have more than one:
 * the Poisson z solve (rows per thread, columns per workgroup, occupancy
   bound, reciprocal flavour), timed on the plan's own buffers;
 * the x and y transforms of the Poisson solve (threads per line, lines per
-  workgroup, radix order: four shapes per direction);
+  workgroup, engine, radix order: four shapes per direction, for y also a
+  persistent launch);
 * the Helmholtz apply (rows per chunk, columns per chunk).
 
 Winners are kept in a JSON cache keyed by GPU architecture, HIP runtime
 version, the library's table of shapes, shape, precision and boundaries (path:
 $PF_TUNE_CACHE, else ~/.cache/pf_channel/tune.json). A corrupt or unreadable
 cache is ignored, and so are entries of another table, whose numbers stand for
-other kernels. poisson_plan applies a cached entry for its grid and precision by default
-(apply_cached_poisson). Tuning runs kernels and may allocate; do it at
+other kernels. poisson_plan applies a cached entry for its grid and precision
+by default (apply_cached_poisson). Tuning runs kernels and may allocate; do it at
 set-up, not inside a graph capture.
 """
 from __future__ import annotations

@@ -872,8 +872,9 @@ pf_status poisson_project(pf_poisson_plan *pl, double *u, double *v, double *w, 
 // Grouped batch: the plans that can share launches (float32 with one
 // float64-residual correction, periodic x and y, a separator-form z solve)
 // run stage by stage; each stage of all plans with the same kernel instance
-// (transform length; z-solve shape and chunk count) is one launch of up to
-// kMaxGroupJobs jobs. The per-plan zero-mode and status kernels run between.
+// (transform length; z-solve shape and row count) is one launch of up to
+// kMaxGroupJobs jobs, the zero mode inside the y forward and the z solve. The
+// per-plan status kernels run between.
 namespace {
 struct GroupKey {
   int a, b;

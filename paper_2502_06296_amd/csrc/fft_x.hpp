@@ -8,7 +8,8 @@
 //
 // Bound by HBM at the copy rate, but for the longest lines (4 passes) and the
 // residual (the latency of its neighbour loads). ms on MI355X, LDS engine and
-// now (float32 inverse: of two spectra):
+// this one (float32 inverse: of two spectra; x_fwd_in_regs, x_inv_in_regs and
+// resid_in_regs say which lengths are left to the LDS engine):
 //   forward  float32  1024 x 512 x 512  0.625 -> 0.600 (5.4 TB/s)   3456 x 3072 x 30  1.16 -> 0.85
 //            float64  3200 x 3456 x 28  1.20 -> 0.98                2048 x 1024 x 128  0.757 -> 0.764
 //   inverse  float32  1024 x 512 x 512  0.806 -> 0.739 (5.8 TB/s)   3456 x 3072 x 30  1.50 -> 1.07

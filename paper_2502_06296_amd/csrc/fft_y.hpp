@@ -6,7 +6,10 @@
 //
 // What bounds it: HBM where the rows are 64 bytes or more and two workgroups
 // share a compute unit; for the long lines one workgroup's loads, exchanges
-// and stores in sequence, and the short row segments (32 float32 bytes).
+// and stores in sequence, and the short row segments (32 float32 bytes). The 864
+// threads of 3456 points leave 128 registers each, of which the forward spills
+// 18-20 (its radix 18 beside the slots 0 and 1), the others 2-22, and the
+// walls' forward of 3200 points 5: 12-76 bytes of scratch a thread.
 // Forward / inverse in ms on MI355X, before (LDS engine) and now:
 //   float32  1024 points, 1024 x 1024 x 512   1.37 / 1.24 -> 0.90 / 0.93  (4.7 TB/s)
 //   float32   512 points, 1024 x 512 x 512    0.49 / 0.48 -> 0.43 / 0.42  (5.0)

@@ -153,9 +153,9 @@ __global__ __launch_bounds__(TPL *LPW) void k_xfwd_div(DivArgs d, T *__restrict_
 // Bound by HBM where the columns alone fill the chip (512 x 384 x 256: 4.9
 // TB/s). With fewer than kProjectBlocks workgroups of columns the planes are
 // cut into chunks of kProjectPlanes or more, blockIdx.z, each of which reads
-// one plane of phi more: the whole substep at 192 x 96 x 100 (72 workgroups
-// of columns) went from 122 to 97 us; at 512 x 384 (768) a cut made it
-// slower, 2.26 -> 2.31 ms.
+// one plane of phi more: 192 x 96 x 100 (72 workgroups of columns) 103 -> 23 us,
+// 512 x 256 x 193 (512, cut in two) 0.436 -> 0.337 ms; at 512 x 384 (768) a cut
+// made the substep slower, 2.26 -> 2.31 ms.
 constexpr long kProjectBlocks = 1024;
 constexpr int kProjectPlanes = 8;
 template <bool LZ>

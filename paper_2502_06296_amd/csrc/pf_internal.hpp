@@ -192,7 +192,9 @@ int y_lines(bool fp64, int n, bool inv, int yw, bool xr, int nx, int nz);
 // LDS engine (512 x 512 x 512 0.298 against 0.312 ms, 1024 x 512 x 512 float64
 // 0.757 / 0.771, 2048 x 1024 x 256 1.50 / 1.53, 3072 points on 2^26 values
 // 0.202 / 0.214), the inverse 512 float32 points (0.383 / 0.403 ms) and the
-// float64 powers of two (1024 x 512 x 512 0.769 / 0.824), the residual 1536
+// float64 powers of two (1024 x 512 x 512 0.769 / 0.824; 384 float32 points
+// 0.87-0.97 of its time on 2^20 to 2^26 values and 1536 float64 points 0.82-0.98
+// are faster here), the residual 1536
 // points (1536 x 512 x 256 0.845 / 0.920). The residual of 384, 768 and 1024
 // points is a little faster there too on small fields (768 on 2^24 values 55 /
 // 61 us, 1024 on 2^22 20 / 22; 1024 x 512 x 512 1.05 / 1.07 ms), but another
@@ -237,12 +239,14 @@ int x_lines(int pass, bool fp64, int n, long pairs);
 // lengths 256, 512, 1024 and 2048 where the length, the 1024-thread and the
 // LDS limits allow them; shapes 0-2 compute the same butterflies (up to the
 // compiler's fusion of multiply-adds), shape 3 in a different order of
-// passes. Where the default y transform is the register engine's, shape 1 is
-// half its lines per workgroup, shape 2 twice them (up to 16) and shape 3 the
-// LDS engine's; the same for the x transforms and the residual.
-// Shape 4 (y transforms only, every length): the default threads and lines
-// in a persistent launch; on the LDS engine it prefetches each workgroup's
-// next block (k_y_persist).
+// passes. On the register engine (y_in_regs, x_fwd_in_regs and the others) shape
+// 1 is half the lines per workgroup of yr_lpw or xr_lpw, shape 2 twice them
+// (the y transforms up to 16: at 512 float32 points the widest default) and
+// shape 3 the LDS engine's.
+// Shape 4 (y transforms only, every length): the default threads and the lines
+// of yr_lpw or y_lpw in a persistent launch; on the LDS engine it prefetches
+// each workgroup's next block (k_y_persist), on the register engine it loads
+// nothing ahead (k_yr_persist).
 constexpr int kTransformShapes = 5;
 constexpr int kYPersistShape = 4;
 constexpr bool tuned_len(int n) { return n == 256 || n == 512 || n == 1024 || n == 2048; }
@@ -418,9 +422,10 @@ int zsolve_default_variant(int nx, int ny, int nz, bool fp64, bool xr);
 
 // ----------------------------------------------------- grouped launches
 // One launch runs one stage of several independent problems that share the
-// kernel instance (transform length; z-solve shape and chunk count):
+// kernel instance (transform length; z-solve shape and row count):
 // blockIdx.y selects the job, blockIdx.x runs over the widest job's blocks,
-// and a job's blocks past its own count exit at once. Float32 storage with
+// and a job's blocks past its own count exit at once (the persistent z solve
+// packs the jobs' workgroups instead, k_zsolve4_grp). Float32 storage with
 // one float64-residual correction, periodic x and y. The fields a stage
 // reads and writes:
 //   x forward:  in = f (float64), out = W (float32), sums = line sums
