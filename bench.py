@@ -434,7 +434,7 @@ def uneven_batch(args):
     # grouped launches on the caller's stream: the 48 Helmholtz fields in
     # launches of up to 16 fields of one chunk height (pcr_apply_batched),
     # then the 16 Poisson solves stage by stage, one launch per transform
-    # length, z-solve shape and chunk count (poisson_solve_batched)
+    # length, z-solve shape and row count (poisson_solve_batched)
     from paper_2502_06296_amd import autotune
     log("bench: uneven batch, grouped launches")
     by_m = {}
